@@ -34,8 +34,8 @@ PEAK_BF16_TFLOPS = 2516.6   # 256 CU x 4096 flop/clk x 2.4 GHz, dense
 PEAK_FP32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 METRIC = "fused LCE fwd+bwd tokens/s and % bf16 MFMA peak (H=4096,V=128256,N=8192)"
-KERNEL_SOURCES = ("paper_2603_16428_amd/csrc/lce_gemm.hpp", "paper_2603_16428_amd/csrc/lce_aux.hpp",
-                  "paper_2603_16428_amd/csrc/lce_api.hip")
+KERNEL_SOURCES = ("paper_2603_16428_amd/csrc/lce_gemm.hpp", "paper_2603_16428_amd/csrc/lce_gemm16.hpp",
+                  "paper_2603_16428_amd/csrc/lce_aux.hpp", "paper_2603_16428_amd/csrc/lce_api.hip")
 
 
 def kernel_source_hash() -> str:

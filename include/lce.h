@@ -83,7 +83,7 @@ typedef enum { LCE_REDUCTION_NONE = 0, LCE_REDUCTION_MEAN = 1, LCE_REDUCTION_SUM
  * a nonzero value smaller than N must be a multiple of 64). The workspace holds
  * O(chunk_tokens * (V + H) + N) elements with backward (one chunk's logits-shaped buffer, two
  * rearranged copies of the chunk's hidden rows, per-token vectors), plus V x H fp32 when dW is
- * carried across chunks in fp32 (see lce_plan_info), and O(chunk_tokens * (V / 64 + H) + N)
+ * carried across chunks in fp32 (see lce_plan_info), and O(chunk_tokens * (V / 8 + H) + N)
  * forward only (per-slice partials instead); the N x V logits never exist. Returns 0 for
  * invalid arguments.
  */

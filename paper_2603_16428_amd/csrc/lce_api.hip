@@ -24,6 +24,7 @@
 #include "lce.h"
 #include "lce_aux.hpp"
 #include "lce_gemm.hpp"
+#include "lce_gemm16.hpp"
 
 // Scratch memory of lce_forward_no_alloc: the workspace of a forward call, in a static device array
 // that every device the library runs on holds (its own copy, at its own address) until the process
@@ -97,6 +98,11 @@ lce_status_t no_alloc_scratch(void** out) {
   return LCE_OK;
 }
 
+// How a contraction is cut into workgroups: gemm_xb_kernel's 256 x 256 (32x32 MFMAs, one wave per
+// SIMD), or gemm_xs_kernel's Tile256, Tile128 (128 x 256, two workgroups per CU), Tile64 or, for the
+// logits of a few tokens, Tile128x64.
+enum GemmTile { TILE_XB = 0, TILE_256 = 1, TILE_128 = 2, TILE_64 = 3, TILE_128x64 = 4 };
+
 struct Plan {
   int64_t N = 0, H = 0, V = 0;
   int esz = 0, dtype = 0;
@@ -108,6 +114,8 @@ struct Plan {
   bool tref = false;
   int64_t nc = 0, chunks = 0;     // tokens per chunk, number of chunks
   int64_t ncp = 0;                // tokens per chunk rounded up to 64
+  GemmTile tile_lg = TILE_XB, tile_dh = TILE_XB, tile_dw = TILE_XB;
+  int slice_rows = kLseSlice;     // vocabulary rows per log-sum-exp partial
   int64_t slices = 0;
   int dh_splits = 1;
   int64_t dh_kps = 0;             // K (vocabulary) per dH split, multiple of the K-tile
@@ -159,13 +167,109 @@ int64_t auto_chunk(int64_t N, int64_t H) {
   return std::max<int64_t>(64, nc);
 }
 
+// The time of one contraction (microseconds, on 256 CUs), to choose between tiles and splits: the
+// busiest CU's tiles one after the other, each a fixed part and `kt` K-tiles of 128 bytes. Measured
+// over N = 64 .. 4096, H = 256 .. 12288, V = 4096 .. 128256. 16-bit, a K-tile: 1.5 us for 256 x 256
+// on a full chip (power-limited; 1.1 on a nearly idle one, whose clock is higher), 0.84 for
+// 128 x 256, 0.30 for 64 x 64. fp32 is bound by its sixteen times slower MFMAs: 3.7 and 0.52.
+double gemm_us(GemmTile t, int esz, int64_t blocks, int64_t kt) {
+  const double rounds = (double)cdiv(blocks, 256);
+  const double fill = (double)blocks / (256.0 * rounds);
+  if (esz == 4) return rounds * (t == TILE_64 ? 2.0 + 0.52 * kt : 4.0 + 3.7 * kt);
+  if (t == TILE_64) return rounds * (1.0 + 0.30 * kt);
+  if (t == TILE_128) return rounds * (4.0 + 0.84 * kt);
+  return rounds * (9.0 + (1.1 + 0.4 * fill) * kt);
+}
+int64_t tile_count(GemmTile t, int64_t M, int64_t N) {
+  if (t == TILE_64) return cdiv(M, Tile64::kBM) * cdiv(N, Tile64::kBN);
+  if (t == TILE_128) return cdiv(M, Tile128::kBM) * cdiv(N, Tile128::kBN);
+  return cdiv(M, kTile) * cdiv(N, kTile);
+}
+// Tile64 where the larger tiles leave CUs idle or are mostly padding, else Tile128.
+GemmTile small_or_128(int esz, int64_t M, int64_t N, int64_t kt) {
+  return gemm_us(TILE_64, esz, tile_count(TILE_64, M, N), kt) < gemm_us(TILE_128, esz, tile_count(TILE_128, M, N), kt)
+             ? TILE_64 : TILE_128;
+}
+
+// logits^T = W . X_c^T: M = V, N = tokens, K = H. Of the large tiles, Tile128 overlaps its epilogues
+// with the other workgroup's main loop (V = 128256, H = 4096, 4096 tokens: 2.93 ms per chunk against
+// 3.16 for gemm_xb_kernel), but moves 1.5 times the operand bytes from L2: gemm_xb_kernel stays ahead
+// where the epilogue is a small part (H = 12288, V = 32768: 2.27 ms against 2.39) and where few
+// columns of tiles reuse W (1000 tokens, H = 4096, V = 128256: 0.82 ms against 0.87; at 2048 tokens
+// 1.64 against 1.58), if its tiles fill their rounds.
+GemmTile logits_tile(int64_t nc, int64_t H, int64_t V, int esz) {
+  const GemmTile t = small_or_128(esz, V, nc, cdiv(H * esz, kTileBytes));
+  // One column of tiles is a stream of W: Tile128x64 leaves a quarter of Tile64's partials to combine
+  // (24 tokens, H = 4096, V = 128256: 189 us a call against 209) where its workgroups fill the CUs
+  // (V = 16384, H = 1024: 20.3 against 19.4).
+  if (t == TILE_64 && esz == 2 && nc <= Tile128x64::kBN && V >= 250 * Tile128x64::kBM) return TILE_128x64;
+  if (t == TILE_64 || esz == 4) return t;
+  const int64_t xb = tile_count(TILE_XB, V, nc);
+  const bool filled = 10 * xb >= 9 * 256 * cdiv(xb, 256);
+  const bool long_k = H >= 8192 || (H >= 2048 && H >= 3 * nc && nc > 256);
+  return long_k && filled ? TILE_XB : TILE_128;
+}
+
+// dW = dZ_c^T . X_c: M = V, N = H, K = tokens. Tile128 (V = 128256, H = 4096, 4096 tokens: 3.09 ms
+// against 3.25 for Tile256 and 3.30 for gemm_xb_kernel), Tile256 for long K and many columns of
+// tiles, whose working set is larger (H = 12288, V = 32768, 4096 tokens: 2.34 against 2.45 ms),
+// gemm_xb_kernel for one column of tiles, where the stream of dZ from HBM is the bound (H = 256,
+// V = 128256, 4096 tokens: 0.257 ms against 0.275).
+GemmTile dw_tile(int64_t nc, int64_t H, int64_t V, int esz) {
+  const GemmTile t = small_or_128(esz, V, H, cdiv(nc * esz, kTileBytes));
+  if (t == TILE_64 || esz == 4 || nc < 4096) return t;
+  return H >= 8192 ? TILE_256 : H <= kTile && V >= 64 * 1024 ? TILE_XB : TILE_128;
+}
+
 bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_BF16 || dtype == LCE_DTYPE_FP16; }
+
+// dH_c^T = W^T . dZ_c^T: M = H, N = tokens, K = V. The grid is small and K long, so K is split where
+// that fills the device: the fp32 partials cost their write and read (about 6 TB/s). (The sum's launch
+// counts as 1 us: at sizes where its few us matter the alternatives are as close.)
+// A split has to win by 5% (at nearly full grids the clock makes up for idle CUs), and its
+// partials stay below the size of W (or 64 MB). Of the 256 x 256 kernels, the eight waves of Tile256
+// are ahead at H > 1024 (H = 4096, V = 128256, 4096 tokens: 2.84 ms against 2.94), gemm_xb_kernel below
+// (H = 768: 0.34 against 0.36). 16-bit Tile128 is for few tokens, where its grid is the finer one; with
+// 2048 and more its operand traffic takes that back (H = 12288, V = 32768: 1.27 ms unsplit, Tile256
+// in two splits the same; H = 4096, V = 128256: 1.63 against 1.51).
+//
+// fp32: an entry's rounding error grows with the length of its running sum, V / splits terms, so Tile128's
+// finer grid may not take splits away: at least as many as fill the device with 256 x 256 tiles, up to
+// eight (8000 tokens, H = 512, V = 20000: dH is 1.4e-6 off in six splits, 0.6e-6 in 32).
+int fp32_min_splits(const Plan& p, int64_t kblocks) {
+  const int64_t tiles = tile_count(TILE_XB, p.H, p.nc);
+  double best = 1e300;
+  int splits = 1;
+  for (int s = 1; s <= std::min<int64_t>(kblocks, 8); ++s) {
+    const double cost = (double)cdiv(tiles * s, 256) / s + (s > 1 ? 0.03 * s : 0.0);
+    if (cost < best - 1e-9) { best = cost; splits = s; }
+  }
+  return splits;
+}
+void plan_dh(Plan& p, int64_t kblocks) {
+  const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 ? TILE_256 : TILE_XB;
+  const int64_t cap = std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
+  const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks) : 1;
+  double best = 1e300;
+  for (const GemmTile t : {big, TILE_128, TILE_64}) {
+    if (t == TILE_128 && p.esz == 2 && p.nc >= 1024) continue;
+    const int64_t tiles = tile_count(t, p.H, p.nc);
+    for (int64_t s = least; s <= std::min<int64_t>(kblocks, 128); ++s) {
+      const int64_t part = s * p.nc * p.H * 4;
+      if (s > least && part > cap) break;
+      double us = gemm_us(t, p.esz, tiles * s, cdiv(kblocks, s));
+      if (s > 1) us = 1.05 * us + 1.0 + 2.0 * (double)part / 6e6;
+      if (us < best) { best = us; p.tile_dh = t; p.dh_splits = (int)s; }
+    }
+  }
+}
 
 // Fills `p`; returns LCE_OK or the status that the sizes deserve.
 // dx_f32: the caller wants d loss / d hidden in fp32 (through the split-K partials even with one
-// split), as the RMSNorm variant does.
+// split), as the RMSNorm variant does. coarse: no 32-row log-sum-exp partials (four times the memory
+// of 128-row ones).
 lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward, int64_t chunk_tokens,
-                       Plan& p, bool query_device, bool dx_f32 = false) {
+                       Plan& p, bool dx_f32 = false, bool coarse = false) {
   if (N < 1 || H < 1 || V < 1 || !dtype_ok(dtype) || chunk_tokens < 0) return LCE_ERR_INVALID_ARGUMENT;
   p.N = N; p.H = H; p.V = V;
   p.esz = dtype == LCE_DTYPE_FP32 ? 4 : 2;
@@ -195,7 +299,11 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   p.nc = nc;
   p.chunks = cdiv(N, nc);
   p.ncp = round_up(nc, 64);
-  p.slices = cdiv(V, kLseSlice);
+  // Forward only: by N, so that the results do not depend on the chunk.
+  p.tile_lg = logits_tile(backward ? nc : N, H, V, p.esz);
+  if (coarse && p.tile_lg == TILE_64) p.tile_lg = TILE_128;
+  p.slice_rows = p.tile_lg == TILE_64 ? Tile64::kSlice : kLseSlice;
+  p.slices = cdiv(V, p.slice_rows);
   // 32-bit limits: buffer ranges of one 256-row operand slice (and of four column blocks of a
   // blocked operand), and int tile/element indices.
   const int64_t lim = (int64_t(1) << 31) - 1;
@@ -211,21 +319,11 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   p.ez_kp = round_up(V, kTile) * p.esz / 32;
 
   if (backward) {
-    // dH tiles of one chunk: split the vocabulary (K) so that the grid fills the device.
-    const int64_t tiles = cdiv(nc, kTile) * cdiv(H, kTile);
-    const int cus = query_device ? num_cus() : 256;
     const int64_t kbk = kTileBytes / p.esz;
     const int64_t kblocks = cdiv(V, kbk);
-    double best = 1e30;
-    int best_s = 1;
-    for (int s = 1; s <= 8; ++s) {
-      if (s > kblocks) break;
-      const double waves = (double)cdiv(tiles * s, cus);
-      const double cost = waves / s + (s > 1 ? 0.03 * s : 0.0);
-      if (cost < best - 1e-9) { best = cost; best_s = s; }
-    }
-    p.dh_splits = best_s;
-    p.dh_kps = cdiv(kblocks, best_s) * kbk;
+    plan_dh(p, kblocks);
+    p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;
+    p.tile_dw = dw_tile(nc, H, V, p.esz);
     p.dw_acc32 = p.esz == 2 && p.chunks > carry_chunks(p.esz, dtype);
   }
 
@@ -262,45 +360,64 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
 // LCE_ERR_WORKSPACE_TOO_SMALL when 64 tokens per chunk are valid but do not fit.
 lce_status_t make_no_alloc_plan(int64_t N, int64_t H, int64_t V, int dtype, Plan& p) {
   const size_t cap = (size_t)LCE_NO_ALLOC_SCRATCH_BYTES;
-  lce_status_t st = make_plan(N, H, V, dtype, false, 0, p, true);
+  lce_status_t st = make_plan(N, H, V, dtype, false, 0, p);
   if (st == LCE_OK && p.total <= cap) return LCE_OK;
   const int64_t top = st == LCE_OK ? p.nc : N;
   Plan q;
-  st = make_plan(N, H, V, dtype, false, 64, q, true);
+  bool coarse = false;
+  st = make_plan(N, H, V, dtype, false, 64, q);
+  if (st == LCE_OK && q.total > cap) {
+    coarse = true;
+    st = make_plan(N, H, V, dtype, false, 64, q, false, coarse);
+  }
   if (st != LCE_OK) return st;
   if (q.total > cap) return LCE_ERR_WORKSPACE_TOO_SMALL;
   int64_t lo = 1, hi = (top - 1) / 64;  // chunks of 64 lo tokens are valid and fit
   while (lo < hi) {
     const int64_t mid = (lo + hi + 1) / 2;
-    if (make_plan(N, H, V, dtype, false, mid * 64, q, true) == LCE_OK && q.total <= cap) lo = mid;
+    if (make_plan(N, H, V, dtype, false, mid * 64, q, false, coarse) == LCE_OK && q.total <= cap) lo = mid;
     else hi = mid - 1;
   }
-  return make_plan(N, H, V, dtype, false, lo * 64, p, true);
+  return make_plan(N, H, V, dtype, false, lo * 64, p, false, coarse);
 }
 
 // AL: operand A's layout (ALayout); operand B is blocked. KCHECK: a K-contig A's K range may end
 // inside a K-tile and its rows are not zero-padded up to the next one (see Operand::offset).
-template <typename T, int EPI, int AL, bool KCHECK = false>
-hipError_t launch_gemm(GemmArgs g, hipStream_t s) {
-  const void* fn = (const void*)gemm_xb_kernel<T, EPI, AL, KCHECK>;
-  static std::atomic<uint64_t> configured[kMaxDevices / 64 + 1];
+hipError_t launch_tiles(void (*fn)(GemmArgs), std::atomic<uint64_t>* configured, int bm, int bn, int threads, int smem,
+                        GemmArgs g, hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < kMaxDevices) {
     const uint64_t bit = uint64_t(1) << (dev & 63);
     if (!(configured[dev >> 6].load() & bit)) {
-      e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kXbSmem);
+      e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
       if (e != hipSuccess) return e;
       configured[dev >> 6].fetch_or(bit);
     }
   }
-  g.tiles_m = (int)cdiv(g.M, kTile);
-  g.tiles_n = (int)cdiv(g.N, kTile);
+  g.tiles_m = (int)cdiv(g.M, bm);
+  g.tiles_n = (int)cdiv(g.N, bn);
+  g.group_m = 1024 / bm;  // tile rows per raster group: 1024 rows of A
   const int blocks = g.tiles_m * g.tiles_n * g.splits;
   if (blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_xb_kernel<T, EPI, AL, KCHECK>), dim3(blocks), dim3(kGemmThreads), kXbSmem, s, g);
+  hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), smem, s, g);
   return hipGetLastError();
+}
+
+template <typename T, int EPI, int AL, bool KCHECK = false>
+hipError_t launch_gemm(GemmTile tile, const GemmArgs& g, hipStream_t s) {
+  static std::atomic<uint64_t> configured[5][kMaxDevices / 64 + 1];
+  auto xs = [&](auto c, int k) {
+    using C = decltype(c);
+    return launch_tiles(gemm_xs_kernel<T, EPI, AL, KCHECK, C>, configured[k], C::kBM, C::kBN, C::kThreads, C::kSmem, g, s);
+  };
+  if (tile == TILE_64) return xs(Tile64{}, 0);
+  if constexpr (EPI == EPI_LSE_FWD || EPI == EPI_LSE_BWD)
+    if (tile == TILE_128x64) return xs(Tile128x64{}, 4);
+  if (tile == TILE_128) return xs(Tile128{}, 1);
+  if (tile == TILE_256) return xs(Tile256{}, 2);
+  return launch_tiles(gemm_xb_kernel<T, EPI, AL, KCHECK>, configured[3], kTile, kTile, kGemmThreads, kXbSmem, g, s);
 }
 
 // Optional events for a caller that streams dW out as it is produced: the last chunk's dW GEMM runs
@@ -354,7 +471,7 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     const int64_t t0 = c * p.nc;
     j.dl_blocks = blocks;
     j.dl = DlogitsJob{ez, p.ez_kp, p.ez_nb, pmax, p.ncp, lse + t0, y + t0, ignore_index, nvalid, mean,
-                      (int)std::min(p.nc, N - t0), (int)V, run_if};
+                      (int)std::min(p.nc, N - t0), (int)V, p.slice_rows, run_if};
   };
   // The call's loss (reduction mean or sum): one block, in a launch after the last combine_kernel.
   auto loss_job = [&](AuxJobs& j) {
@@ -398,7 +515,6 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     g.B = xk; g.ldb = p.xk_kp; g.N = rows;
     g.K = (int)H;
     g.splits = 1; g.k_per_split = (int)round_up(H, kTileBytes / p.esz);
-    g.group_m = 4;
     g.pmax = pmax; g.psum = psum; g.ldp = p.ncp;
     hipError_t e;
     {
@@ -408,22 +524,31 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     if (p.backward) {
       g.out = ez; g.ldo = p.ez_kp;
       if (p.tref) g.ref = tref + t0;
-      e = whole ? launch_gemm<T, EPI_LSE_BWD, A_K, false>(g, s) : launch_gemm<T, EPI_LSE_BWD, A_K, true>(g, s);
+      e = whole ? launch_gemm<T, EPI_LSE_BWD, A_K, false>(p.tile_lg, g, s) : launch_gemm<T, EPI_LSE_BWD, A_K, true>(p.tile_lg, g, s);
     } else {
-      e = whole ? launch_gemm<T, EPI_LSE_FWD, A_K, false>(g, s) : launch_gemm<T, EPI_LSE_FWD, A_K, true>(g, s);
+      e = whole ? launch_gemm<T, EPI_LSE_FWD, A_K, false>(p.tile_lg, g, s) : launch_gemm<T, EPI_LSE_FWD, A_K, true>(p.tile_lg, g, s);
     }
     }
     if (e != hipSuccess) return LCE_ERR_HIP;
 
-    auto combine = [&](int mode, const int* run_if) {
+    auto combine = [&](auto mode_c, const int* run_if) {
       KernelTimer t(T_OTHER, s);
-      hipLaunchKernelGGL((combine_kernel<T>), dim3((unsigned)cdiv(rows, kCombineTokens)), dim3(256), 0, s, pmax, psum,
-                         p.ncp, (int)p.slices, rows, y + t0, ignore_index, tgt + t0, lse + t0, tl + t0, mode,
-                         scale ? scale + t0 : nullptr, (const int*)nvalid, mean, ez, p.ez_kp, V,
-                         flags ? flags + c : nullptr, run_if);
+      auto launch = [&](auto tok) {
+        constexpr int TOK = decltype(tok)::value, MODE = decltype(mode_c)::value;
+        hipLaunchKernelGGL((combine_kernel<T, TOK, MODE>), dim3((unsigned)cdiv(rows, TOK)), dim3(kCombineThreads), 0, s,
+                           pmax, psum, p.ncp, (int)p.slices, rows, y + t0, ignore_index, tgt + t0, lse + t0, tl + t0,
+                           scale ? scale + t0 : nullptr, (const int*)nvalid, mean, ez, p.ez_kp, V,
+                           flags ? flags + c : nullptr, run_if);
+      };
+      // Few tokens: more blocks, and more threads per token.
+      if (rows <= 256) launch(std::integral_constant<int, 4>{});
+      else launch(std::integral_constant<int, 16>{});
       return hipGetLastError();
     };
-    if (combine(p.tref ? CMB_TREF : CMB_FORWARD, nullptr) != hipSuccess) return LCE_ERR_HIP;
+    using Tref = std::integral_constant<int, CMB_TREF>;
+    using Forward = std::integral_constant<int, CMB_FORWARD>;
+    using Slice = std::integral_constant<int, CMB_SLICE>;
+    if ((p.tref ? combine(Tref{}, nullptr) : combine(Forward{}, nullptr)) != hipSuccess) return LCE_ERR_HIP;
     if (!p.backward) {
       if (last_chunk) {
         AuxJobs j{};
@@ -453,10 +578,10 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
       {
       KernelTimer t(T_OTHER, s);
       const bool whole = H % (kTileBytes / p.esz) == 0;
-      e = whole ? launch_gemm<T, EPI_LSE_BWD, A_K, false>(gf, s) : launch_gemm<T, EPI_LSE_BWD, A_K, true>(gf, s);
+      e = whole ? launch_gemm<T, EPI_LSE_BWD, A_K, false>(p.tile_lg, gf, s) : launch_gemm<T, EPI_LSE_BWD, A_K, true>(p.tile_lg, gf, s);
       }
       if (e != hipSuccess) return LCE_ERR_HIP;
-      if (combine(CMB_SLICE, flag) != hipSuccess) return LCE_ERR_HIP;
+      if (combine(Slice{}, flag) != hipSuccess) return LCE_ERR_HIP;
       dl_job(tail, c, flag, std::min<int64_t>(p.ez_kp / 16 * p.ez_nb, (int64_t)num_cus()));
       bmn_job(tail, c, scale + t0);
       if (aux(tail, T_OTHER) != hipSuccess) return LCE_ERR_HIP;
@@ -473,7 +598,6 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     gh.B = ez; gh.ldb = p.ez_kp; gh.N = rows;
     gh.K = (int)V;
     gh.splits = p.dh_splits; gh.k_per_split = (int)p.dh_kps;
-    gh.group_m = 4;
     if (p.dh_splits > 1 || dx32) {
       gh.out = dhp; gh.ldo = H; gh.mode = 1;
     } else {
@@ -483,16 +607,14 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     if (p.tref) gh.col_scale = scale + t0;
     {
     KernelTimer t(T_DH, s);
-    if (launch_gemm<T, EPI_STORE, A_MN>(gh, s) != hipSuccess) return LCE_ERR_HIP;
+    if (launch_gemm<T, EPI_STORE, A_MN>(p.tile_dh, gh, s) != hipSuccess) return LCE_ERR_HIP;
     if (dx32) {
       const int64_t count = (int64_t)rows * H;
-      hipLaunchKernelGGL((split_reduce_kernel<float, T>), dim3((unsigned)cdiv(count / 4, 256)), dim3(256), 0, s, dhp,
-                         p.dh_splits, count, dx32 + t0 * H, (const int*)nvalid, mean);
+      launch_split_reduce<float, T>(dhp, p.dh_splits, count, dx32 + t0 * H, nvalid, mean, s);
       if (hipGetLastError() != hipSuccess) return LCE_ERR_HIP;
     } else if (p.dh_splits > 1) {
       const int64_t count = (int64_t)rows * H;
-      hipLaunchKernelGGL((split_reduce_kernel<T>), dim3((unsigned)cdiv(count / 4, 256)), dim3(256), 0, s, dhp,
-                         p.dh_splits, count, dH + t0 * H, (const int*)nvalid, mean);
+      launch_split_reduce<T, T>(dhp, p.dh_splits, count, dH + t0 * H, nvalid, mean, s);
       if (hipGetLastError() != hipSuccess) return LCE_ERR_HIP;
     }
     }
@@ -503,7 +625,6 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     gw.B = xm; gw.ldb = p.xm_kp; gw.N = (int)H;
     gw.K = rows;
     gw.splits = 1; gw.k_per_split = (int)round_up(rows, kTileBytes / p.esz);
-    gw.group_m = 4;
     gw.out = dW; gw.ldo = H;
     const bool last = c == p.chunks - 1;
     gw.mode = c == 0 ? DW_STORE : DW_ACCUMULATE;
@@ -527,13 +648,13 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
           gb.out = dW + r0 * H;
           if (gb.acc32) gb.acc32 += r0 * H;
           KernelTimer t(T_DW, s);
-          if (launch_gemm<T, EPI_DW, A_BLK>(gb, s) != hipSuccess) return LCE_ERR_HIP;
+          if (launch_gemm<T, EPI_DW, A_BLK>(p.tile_dw, gb, s) != hipSuccess) return LCE_ERR_HIP;
         }
         if (hipEventRecord(hook->dw_done[b], s) != hipSuccess) return LCE_ERR_HIP;
       }
     } else {
     KernelTimer t(T_DW, s);
-    if (launch_gemm<T, EPI_DW, A_BLK>(gw, s) != hipSuccess) return LCE_ERR_HIP;
+    if (launch_gemm<T, EPI_DW, A_BLK>(p.tile_dw, gw, s) != hipSuccess) return LCE_ERR_HIP;
     }
   }
 
@@ -550,8 +671,8 @@ struct RmsPlan {
 };
 
 lce_status_t make_rms_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward, int64_t chunk_tokens,
-                           RmsPlan& rp, bool query_device) {
-  lce_status_t st = make_plan(N, H, V, dtype, backward, chunk_tokens, rp.lce, query_device, backward);
+                           RmsPlan& rp) {
+  lce_status_t st = make_plan(N, H, V, dtype, backward, chunk_tokens, rp.lce, backward);
   if (st != LCE_OK) return st;
   size_t off = rp.lce.total;
   auto take = [&](size_t bytes) {
@@ -756,13 +877,13 @@ extern "C" {
 
 size_t lce_workspace_size(int64_t N, int64_t H, int64_t V, int dtype, int with_backward, int64_t chunk_tokens) {
   lce::Plan p;
-  if (lce::make_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, p, true) != LCE_OK) return 0;
+  if (lce::make_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, p) != LCE_OK) return 0;
   return p.total;
 }
 
 int64_t lce_auto_chunk_tokens(int64_t N, int64_t H, int64_t V, int dtype) {
   lce::Plan p;
-  if (lce::make_plan(N, H, V, dtype, true, 0, p, false) != LCE_OK) return 0;
+  if (lce::make_plan(N, H, V, dtype, true, 0, p) != LCE_OK) return 0;
   return p.nc;
 }
 
@@ -770,7 +891,7 @@ lce_status_t lce_plan_info(int64_t N, int64_t H, int64_t V, int dtype, int with_
                            lce_plan_info_t* info) {
   if (!info) return LCE_ERR_INVALID_ARGUMENT;
   lce::Plan p;
-  const lce_status_t st = lce::make_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, p, true);
+  const lce_status_t st = lce::make_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, p);
   if (st != LCE_OK) return st;
   std::memset(info, 0, sizeof(*info));
   info->chunk_tokens = p.nc;
@@ -790,7 +911,7 @@ lce_status_t lce_forward(const void* hidden, const void* weight, const int64_t* 
   if (reduction != LCE_REDUCTION_NONE && reduction != LCE_REDUCTION_MEAN && reduction != LCE_REDUCTION_SUM)
     return LCE_ERR_INVALID_ARGUMENT;
   lce::Plan p;
-  lce_status_t st = lce::make_plan(N, H, V, dtype, false, 0, p, true);
+  lce_status_t st = lce::make_plan(N, H, V, dtype, false, 0, p);
   if (st != LCE_OK) return st;
   if (!workspace || workspace_bytes < p.total) return LCE_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
@@ -834,7 +955,7 @@ lce_status_t lce_forward_backward(const void* hidden, const void* weight, const 
   if (!hidden || !weight || !labels || !loss || !grad_hidden || !grad_weight) return LCE_ERR_INVALID_ARGUMENT;
   if (reduction != LCE_REDUCTION_MEAN && reduction != LCE_REDUCTION_SUM) return LCE_ERR_INVALID_ARGUMENT;
   lce::Plan p;
-  lce_status_t st = lce::make_plan(N, H, V, dtype, true, chunk_tokens, p, true);
+  lce_status_t st = lce::make_plan(N, H, V, dtype, true, chunk_tokens, p);
   if (st != LCE_OK) return st;
   if (!workspace || workspace_bytes < p.total) return LCE_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
@@ -853,7 +974,7 @@ lce_status_t lce_forward_backward(const void* hidden, const void* weight, const 
 size_t lce_rmsnorm_workspace_size(int64_t N, int64_t H, int64_t V, int dtype, int with_backward,
                                   int64_t chunk_tokens) {
   lce::RmsPlan rp;
-  if (lce::make_rms_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, rp, true) != LCE_OK) return 0;
+  if (lce::make_rms_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, rp) != LCE_OK) return 0;
   return rp.total;
 }
 
@@ -865,7 +986,7 @@ lce_status_t lce_rmsnorm_forward(const void* hidden, const void* gamma, const vo
   if (reduction != LCE_REDUCTION_NONE && reduction != LCE_REDUCTION_MEAN && reduction != LCE_REDUCTION_SUM)
     return LCE_ERR_INVALID_ARGUMENT;
   lce::RmsPlan rp;
-  lce_status_t st = lce::make_rms_plan(N, H, V, dtype, false, 0, rp, true);
+  lce_status_t st = lce::make_rms_plan(N, H, V, dtype, false, 0, rp);
   if (st != LCE_OK) return st;
   if (!workspace || workspace_bytes < rp.total) return LCE_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
@@ -893,7 +1014,7 @@ lce_status_t lce_rmsnorm_forward_backward(const void* hidden, const void* gamma,
     return LCE_ERR_INVALID_ARGUMENT;
   if (reduction != LCE_REDUCTION_MEAN && reduction != LCE_REDUCTION_SUM) return LCE_ERR_INVALID_ARGUMENT;
   lce::RmsPlan rp;
-  lce_status_t st = lce::make_rms_plan(N, H, V, dtype, true, chunk_tokens, rp, true);
+  lce_status_t st = lce::make_rms_plan(N, H, V, dtype, true, chunk_tokens, rp);
   if (st != LCE_OK) return st;
   if (!workspace || workspace_bytes < rp.total) return LCE_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
@@ -926,7 +1047,7 @@ lce_status_t lce_head_train_step(const void* hidden, const int64_t* labels, int6
   if (dtype != LCE_DTYPE_BF16 && dtype != LCE_DTYPE_FP16) return dtype == LCE_DTYPE_FP32 ? LCE_ERR_UNSUPPORTED
                                                                                         : LCE_ERR_INVALID_ARGUMENT;
   lce::Plan p;
-  lce_status_t st = lce::make_plan(N, H, V, dtype, true, chunk_tokens, p, true);
+  lce_status_t st = lce::make_plan(N, H, V, dtype, true, chunk_tokens, p);
   if (st != LCE_OK) return st;
   if (!workspace || workspace_bytes < p.total) return LCE_ERR_WORKSPACE_TOO_SMALL;
   // The optimizer settings are checked before any GPU work.

@@ -108,9 +108,15 @@ __device__ __forceinline__ void loss_sum_block(const float* __restrict__ tl, int
 }
 
 // Row combine. For each token of the chunk: M = max_t m_t, lse = M + log sum_t s_t exp(m_t - M),
-// and the token loss lse - z_target (0 for ignored tokens). A block takes 16 tokens x 16 slice
-// groups: thread (token j, group k) merges slices k, k + 16, ... in increasing order (a 64-byte
-// coalesced row of partials per slice), then group 0 merges the 16 groups in a fixed order.
+// and the token loss lse - z_target (0 for ignored tokens). A block of 1024 threads takes
+// TOK = 16 tokens x 64 slice groups, or 4 x 256: thread (token j, group k) merges slices k, k +
+// groups, ... in increasing order (64- or 16-byte pieces of the slices' rows), then a wave's groups
+// are merged across its lanes and the 16 waves' sums by one thread per token, in a fixed order. The
+// partials are a few MB that come from HBM like the code itself (the GEMM before has streamed W
+// through every cache): what counts is how many threads share the chain of loads, and how few
+// instructions there are to fetch (hence a kernel per mode, and the sums unrolled only where loads
+// overlap). With 16 groups merging pairwise, 4096 tokens (V = 128256) took 17 us here, now 10; 24
+// tokens 20 us in two blocks, now 10 in six.
 //
 // Backward, the per-token factor that the dH epilogue and the dW operand apply (scale_out):
 //   CMB_TREF  : e holds exp(z - z_target) for valid tokens (label in [0, V), not ignored), and the
@@ -128,69 +134,97 @@ __device__ __forceinline__ void loss_sum_block(const float* __restrict__ tl, int
 enum CombineMode { CMB_FORWARD = 0, CMB_TREF = 1, CMB_SLICE = 2 };
 constexpr float kTrefMaxSum = 1.1420073898e26f;  // exp(60)
 constexpr float kTrefMinSum = 0.5f;
-constexpr int kCombineTokens = 16;
-template <typename T>
-__global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ pmax, const float* __restrict__ psum,
+constexpr int kCombineThreads = 1024;
+template <typename T, int TOK, int MODE>
+__global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* __restrict__ pmax, const float* __restrict__ psum,
                                                       int64_t ldp, int slices, int rows,
                                                       const int64_t* __restrict__ y, int64_t ignore_index,
                                                       const float* __restrict__ tgt,
                                                       float* __restrict__ lse_out,     // [rows] (chunk-offset)
                                                       float* __restrict__ loss_out,    // [rows] (chunk-offset)
-                                                      int mode, float* __restrict__ scale_out,
+                                                      float* __restrict__ scale_out,
                                                       const int* __restrict__ n_valid, int mean, T* __restrict__ ez,
                                                       int64_t KP, int64_t V, int* __restrict__ flag,
                                                       const int* __restrict__ run_if) {
   if (run_if != nullptr && *run_if == 0) return;
-  __shared__ float sm[16][kCombineTokens], ss[16][kCombineTokens];
-  const int t = threadIdx.x % kCombineTokens, grp = threadIdx.x / kCombineTokens;
-  const int i = blockIdx.x * kCombineTokens + t;
-  float m = -INFINITY, s = 0.f;
+  constexpr int kWaves = kCombineThreads / 64, kGroups = kCombineThreads / TOK;
+  __shared__ float sm[kWaves][TOK], ss[kWaves][TOK];
+  const int t = threadIdx.x % TOK, grp = threadIdx.x / TOK;
+  const int i = blockIdx.x * TOK + t;
   // Target-referenced partials all share one reference per token (its target logit, or 0 for a
-  // token without one), so the maxima are not read: the merge below runs with 0 in their place,
-  // where every factor exp(m - mn) is exactly 1 as it would be with the reference itself, and the
+  // token without one), so the maxima are not read: the sums add up with 0 in their place, and the
   // reference is added back to the merged maximum.
-  const bool shared_ref = mode == CMB_TREF;
+  constexpr bool kShared = MODE == CMB_TREF;
+  float m = kShared ? 0.f : -INFINITY, s = 0.f;
   if (i < rows) {
-    // Eight slices' partials are requested before any is merged (the merge order is unchanged).
-    constexpr int kAhead = 8;
-    for (int k0 = grp; k0 < slices; k0 += 16 * kAhead) {
+    // Sixteen slices' partials are requested before any is merged.
+    constexpr int kAhead = 16;
+#pragma unroll 1
+    for (int k0 = grp; k0 < slices; k0 += kGroups * kAhead) {
       float mk[kAhead], sk[kAhead];
+      float mn = m;
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        const int k = min(k0 + 16 * u, slices - 1);
-        mk[u] = shared_ref ? 0.f : pmax[(size_t)k * ldp + i];
-        sk[u] = psum[(size_t)k * ldp + i];
+        const int k = k0 + kGroups * u;
+        const size_t o = (size_t)min(k, slices - 1) * ldp + i;
+        if constexpr (!kShared) {
+          mk[u] = pmax[o];
+          if (k >= slices) mk[u] = -INFINITY;
+        }
+        sk[u] = psum[o];
+        if (k >= slices) sk[u] = 0.f;
       }
+      if constexpr (kShared) {
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        if (k0 + 16 * u >= slices) break;
-        const float mn = fmaxf(m, mk[u]);
-        s = s * __expf(m - mn) + sk[u] * __expf(mk[u] - mn);
+        for (int u = 0; u < kAhead; ++u) s += sk[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) mn = fmaxf(mn, mk[u]);
+        s *= __expf(m - mn);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) s = fmaf(sk[u], __expf(mk[u] - mn), s);
         m = mn;
       }
     }
   }
-  sm[grp][t] = m;
-  ss[grp][t] = s;
+#pragma unroll
+  for (int o = TOK; o < 64; o <<= 1) {
+    const float s2 = __shfl_xor(s, o);
+    if constexpr (kShared) {
+      s += s2;
+    } else {
+      // A group without slices has m = -inf and s = 0 (equal maxima: factor 1, also for two of those).
+      const float m2 = __shfl_xor(m, o);
+      const float mn = fmaxf(m, m2);
+      s = s * (m == mn ? 1.f : __expf(m - mn)) + s2 * (m2 == mn ? 1.f : __expf(m2 - mn));
+      m = mn;
+    }
+  }
+  if ((threadIdx.x & 63) < TOK) {
+    sm[threadIdx.x >> 6][t] = m;
+    ss[threadIdx.x >> 6][t] = s;
+  }
   __syncthreads();
   if (grp == 0 && i < rows) {
-    float M = sm[0][t];
-    for (int k = 1; k < 16; ++k) M = fmaxf(M, sm[k][t]);
-    float S = 0.f;
-    for (int k = 0; k < 16; ++k) S += ss[k][t] * __expf(sm[k][t] - M);
-    const int64_t lab = y[i];
-    if (shared_ref) {
-      // The logits epilogue's reference: the target logit of a valid token when finite, else 0.
-      const float r = tgt[i];
-      M = (lab != ignore_index && lab >= 0 && lab < V && __builtin_isfinite(r)) ? r : 0.f;
+    float M = sm[0][t], S = 0.f;
+    if constexpr (!kShared) {
+#pragma unroll 1
+      for (int k = 1; k < kWaves; ++k) M = fmaxf(M, sm[k][t]);
     }
+#pragma unroll 1
+    for (int k = 0; k < kWaves; ++k) S += kShared ? ss[k][t] : ss[k][t] * __expf(sm[k][t] - M);
+    const int64_t lab = y[i];
+    const float target = tgt[i];
+    const bool valid = lab != ignore_index && lab >= 0 && lab < V;
+    // The logits epilogue's reference: the target logit of a valid token when finite, else 0.
+    if constexpr (kShared) M = (valid && __builtin_isfinite(target)) ? target : 0.f;
     const float lse = M + __logf(S);
     lse_out[i] = lse;
-    loss_out[i] = (lab == ignore_index) ? 0.f : lse - tgt[i];
-    if (mode == CMB_TREF) {
+    loss_out[i] = (lab == ignore_index) ? 0.f : lse - target;
+    if constexpr (MODE == CMB_TREF) {
       float sc = 0.f;
-      if (lab != ignore_index && lab >= 0 && lab < V) {
-        const float sum = S * __expf(M - tgt[i]);  // every m_t is tgt[i] here, so this is S
+      if (valid) {
+        const float sum = S * __expf(M - target);  // M is the target here, so this is S
         if (sum >= kTrefMinSum && sum <= kTrefMaxSum) {  // (NaN fails both)
           const int nv = *n_valid;
           const float g = mean ? (nv > 0 ? 1.f / (float)nv : 0.f) : 1.f;
@@ -205,7 +239,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
         }
       }
       scale_out[i] = sc;
-    } else if (mode == CMB_SLICE) {
+    } else if constexpr (MODE == CMB_SLICE) {
       scale_out[i] = 1.f;
     }
   }
@@ -219,15 +253,15 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 // where e = exp(z - m_t,i) was stored by the logits GEMM. Every piece of the buffer is written:
 // tokens at or beyond `rows` and ids at or beyond V as zeros (the dW GEMM sums over the last token
 // block, the dH GEMM reads the id padding). Block (b, jb) covers K-pairs 16 b .. 16 b + 15 of token
-// block jb (KP is a multiple of 16); wave w takes K-pairs 16 b + 4 w .. + 3, which lie in one
-// slice, so each lane has one token and one scale. For fp16 both e and dZ carry the storage
+// block jb (KP is a multiple of 16); wave w takes K-pairs 16 b + 4 w .. + 3, of which each two lie
+// in one slice (slice_rows: 128 ids or 32), so each lane has one token and two scales. For fp16 both e and dZ carry the storage
 // scales of Storage<f16> (dZ = (p - onehot) kDz for valid tokens; g is applied later).
 template <typename T>
 __device__ __forceinline__ void dlogits_block(T* __restrict__ ez, int64_t KP, int64_t bx, int jb,
                                               const float* __restrict__ pmax, int64_t ldp,
                                               const float* __restrict__ lse, const int64_t* __restrict__ y,
                                               int64_t ignore_index, const int* __restrict__ n_valid, int mean,
-                                              int rows, int V) {
+                                              int rows, int V, int slice_rows) {
   constexpr int kVec = 16 / sizeof(T);          // ids per piece
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t q0 = 16 * bx + 4 * w;
@@ -242,14 +276,18 @@ __device__ __forceinline__ void dlogits_block(T* __restrict__ ez, int64_t KP, in
   const int64_t lab = y[ic];
   const bool active = i < rows && lab != ignore_index;
   const int v0 = (int)((q0 * 32 + 16 * (l >> 5)) / (int)sizeof(T));
-  const int slice = min(v0, V - 1) / kLseSlice;
   const int nv = *n_valid;
   const float g = Storage<T>::kDzUnscaled ? Storage<T>::kDz : (mean ? (nv > 0 ? 1.f / (float)nv : 0.f) : 1.f);
   constexpr float kInvE = 1.f / Storage<T>::kE;
-  const float c = g * kInvE * __expf(pmax[(size_t)slice * ldp + i] - lse[ic]);
+  constexpr int kIds = 32 / (int)sizeof(T);     // ids per K-pair
+  float cs[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    cs[u] = g * kInvE * __expf(pmax[(size_t)(min(v0 + 2 * u * kIds, V - 1) / slice_rows) * ldp + i] - lse[ic]);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int v = v0 + k * (32 / (int)sizeof(T));
+    const int v = v0 + k * kIds;
+    const float c = cs[k >> 1];
     T ev[kVec], outv[kVec];
     *(uint4*)ev = raw[k];
 #pragma unroll
@@ -273,7 +311,7 @@ struct DlogitsJob {
   const int64_t* y;
   int64_t ignore_index;
   const int* n_valid;
-  int mean, rows, V;
+  int mean, rows, V, slice_rows;
   const int* run_if;
 };
 
@@ -283,30 +321,59 @@ __device__ __forceinline__ void dlogits_job(int64_t b, int64_t blocks, const Dlo
   const int64_t nbx = a.KP / 16;
   for (int64_t idx = b; idx < nbx * a.NB; idx += blocks)
     dlogits_block<T>((T*)a.ez, a.KP, idx % nbx, (int)(idx / nbx), a.pmax, a.ldp, a.lse, a.y, a.ignore_index,
-                     a.n_valid, a.mean, a.rows, a.V);
+                     a.n_valid, a.mean, a.rows, a.V, a.slice_rows);
 }
 
 // out[i][h] = sum_s part[s][i][h] (fixed order), times the dz storage scale's inverse of the
-// operand type TS (1 unless dz is stored unscaled), converted to the output type T.
-template <typename T, typename TS = T>
+// operand type TS (1 unless dz is stored unscaled), converted to the output type T. G threads share
+// the splits of four values, each taking every G-th (four loads in flight), and the first sums the G
+// results: with G = 1 the many splits of a small dH were one thread's chain of loads (256 x 64
+// values in 128 splits: 45 us, the contraction itself 16).
+constexpr int kReduceGroups = 8;  // G for at least as many splits, else 1
+template <typename T, typename TS, int G>
 __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restrict__ part, int splits,
                                                            int64_t count, T* __restrict__ out,
                                                            const int* __restrict__ n_valid, int mean) {
-  const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  constexpr int kCols = 256 / G;
+  const int grp = threadIdx.x / kCols;
+  const int64_t idx = ((int64_t)blockIdx.x * kCols + threadIdx.x % kCols) * 4;
+  f32x4 s = {};
+  if (idx < count) {
+    constexpr int kAhead = 4;
+    for (int k0 = grp; k0 < splits; k0 += G * kAhead) {
+      f32x4 v[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        v[u] = k0 + G * u < splits ? *(const f32x4*)(part + (size_t)(k0 + G * u) * count + idx) : (f32x4){};
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) s += v[u];
+    }
+  }
+  if constexpr (G > 1) {
+    __shared__ f32x4 sums[G][kCols];
+    sums[grp][threadIdx.x % kCols] = s;
+    __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int k = 1; k < G; ++k) s += sums[k][threadIdx.x];
+  }
   if (idx >= count) return;
-  float4 s = *(const float4*)(part + idx);
-  for (int k = 1; k < splits; ++k) {
-    const float4 v = *(const float4*)(part + (size_t)k * count + idx);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  if constexpr (Storage<TS>::kDzUnscaled) s *= dz_epilogue_scale<TS>(n_valid, mean);
+  store4(out + idx, s[0], s[1], s[2], s[3]);
+}
+
+template <typename T, typename TS>
+void launch_split_reduce(const float* part, int splits, int64_t count, T* out, const int* n_valid, int mean,
+                         hipStream_t s) {
+  const int64_t pieces = count / 4;  // H is a multiple of 4 (16-bit: 8)
+  if (splits >= kReduceGroups) {
+    constexpr int kCols = 256 / kReduceGroups;
+    hipLaunchKernelGGL((split_reduce_kernel<T, TS, kReduceGroups>), dim3((unsigned)((pieces + kCols - 1) / kCols)),
+                       dim3(256), 0, s, part, splits, count, out, n_valid, mean);
+  } else {
+    hipLaunchKernelGGL((split_reduce_kernel<T, TS, 1>), dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, part,
+                       splits, count, out, n_valid, mean);
   }
-  if constexpr (Storage<TS>::kDzUnscaled) {
-    const float sc = dz_epilogue_scale<TS>(n_valid, mean);
-    s.x *= sc; s.y *= sc; s.z *= sc; s.w *= sc;
-  }
-  out[idx] = from_f32<T>(s.x);
-  out[idx + 1] = from_f32<T>(s.y);
-  out[idx + 2] = from_f32<T>(s.z);
-  out[idx + 3] = from_f32<T>(s.w);
 }
 
 // One launch for several independent bandwidth-bound jobs, each on its own consecutive range of

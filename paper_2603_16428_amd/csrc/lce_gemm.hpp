@@ -63,7 +63,7 @@ constexpr int kTile = 256;                       // BM = BN
 constexpr int kTileBytes = 128;                  // bytes of K per row of a K-contig K-tile
 constexpr int kOperandBytes = 32 * 1024;         // one operand's K-tile in LDS
 constexpr int kGemmThreads = 256;
-constexpr int kLseSlice = 128;                   // vocabulary rows per log-sum-exp partial
+constexpr int kLseSlice = 128;                   // vocabulary rows per log-sum-exp partial (a wave's)
 constexpr uint32_t kOOB = 0x80000000u;           // a buffer offset beyond every range check
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -303,6 +303,7 @@ struct Operand {
   const char* base;   // element (mn0, 0)
   int64_t ld;
   int kb, ke;         // K range of this split
+  uint32_t skip;      // MN-contig: bytes of a K-row before the tile's first column
   // Byte offset of load j within a K-tile = row_off + j * row_step + (slot_x ^ xor_j(j)): a lane
   // term, a uniform term and a compile-time XOR (the kernel forms the eight per-lane terms once).
   uint32_t row_off, slot_x, row_step;
@@ -314,6 +315,7 @@ struct Operand {
     ld = ld_;
     kb = kb_;
     ke = ke_;
+    skip = (uint32_t)mn0 * kEsz;
     if constexpr (!MN) {
       base = (const char*)p + (size_t)mn0 * ld * kEsz;
       rsrc_k = make_rsrc((const void*)uniform64((uint64_t)base),
@@ -409,8 +411,10 @@ struct Operand {
       const int k0 = kb + t * kBK;
       const int nrows = max(0, min(kBK, ke - k0));
       const char* p = base + (size_t)(k0 < ke ? k0 : kb) * ld * kEsz;
+      // The range ends with the last K-row's own columns: what follows is other memory.
       return make_rsrc((const void*)uniform64((uint64_t)p),
-                       __builtin_amdgcn_readfirstlane((uint32_t)nrows * (uint32_t)ld * kEsz));
+                       __builtin_amdgcn_readfirstlane((uint32_t)nrows * (uint32_t)ld * kEsz -
+                                                      (uint32_t)min(nrows, 1) * skip));
     }
   }
 
@@ -672,13 +676,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
                 // at or beyond M hold exp = 0 here.
                 store_frag32<T>(e_blk + (size_t)((mw + 32 * i) >> 4) * 1024, ev);
               } else {
-                // fp32: a K-pair is 8 ids, half of it per lane half. The dH GEMM reads every K-pair
-                // that holds an id below M whole, so such a K-pair is stored whole: its ids at or
-                // beyond M hold exp = 0 here, and nothing stale from the workspace reaches it.
+                // fp32: a K-pair is 8 ids, half of it per lane half. The dH GEMMs read every K-quad
+                // (16 ids) that holds an id below M whole, so such a K-quad is stored whole: its ids
+                // at or beyond M hold exp = 0 here, and nothing stale from the workspace reaches it.
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                   const int kp_row = mw + 32 * i + 8 * q;
-                  if (FULL || kp_row < g.M)
+                  if (FULL || (kp_row & ~15) < g.M)
                     store4((T*)(e_blk + (size_t)(kp_row >> 3) * 1024), ev[4 * q], ev[4 * q + 1], ev[4 * q + 2],
                            ev[4 * q + 3]);
                 }
@@ -1137,9 +1141,9 @@ __device__ __forceinline__ void gemm_xb_tile(const GemmArgs& g, int bid, char* s
         pair_delta = -pair_delta;
       }
     }
-    // Loads past the end may still be in flight (they target no memory); their LDS and registers
-    // must not be reused before they retire.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // Loads past the end may still be in flight (they target no memory), and the last section's
+    // fragment reads; their LDS and registers must not be reused before they retire.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   }
 
   gemm_epilogue<T, EPI, kPreload>(g, acc, mw, nw, split, accumulate, n0, smem + kXbRefs);
