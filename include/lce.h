@@ -76,16 +76,17 @@ typedef enum { LCE_REDUCTION_NONE = 0, LCE_REDUCTION_MEAN = 1, LCE_REDUCTION_SUM
 /*
  * Bytes of device workspace needed by lce_forward (with_backward = 0) or lce_forward_backward
  * (with_backward = 1) for these sizes. chunk_tokens is the number of tokens processed per chunk
- * (0 = automatic: with backward, the largest multiple of 64 not above min(H, ceil(N/2)), at least
- * 64, raised to ceil(N / limit) rounded up to 64 when that keeps the chunk count within dW's carry
- * limit (BF16 4, FP16 9; see lce_plan_info) and is at most 2 H; forward only, all N tokens up to
- * 16384, else chunks of 16384 or the backward size if larger;
+ * (0 = automatic: with backward, all N tokens up to min(H, 2048), else min(H rounded down to 64,
+ * N/2 rounded up to 64), at least 64, raised to ceil(N / limit) rounded up to 64 when that keeps the
+ * chunk count within dW's carry limit (BF16 4, FP16 9; see lce_plan_info) and is at most 2 H;
+ * forward only, all N tokens up to 16384, else chunks of 16384 or the backward size if larger;
  * a nonzero value smaller than N must be a multiple of 64). The workspace holds
  * O(chunk_tokens * (V + H) + N) elements with backward (one chunk's logits-shaped buffer, two
  * rearranged copies of the chunk's hidden rows, per-token vectors), plus V x H fp32 when dW is
  * carried across chunks in fp32 (see lce_plan_info), and O(chunk_tokens * (V / 8 + H) + N)
- * forward only (per-slice partials instead); the N x V logits never exist. Returns 0 for
- * invalid arguments.
+ * forward only (per-slice partials instead); the logits-shaped buffer is never larger than W, or
+ * than twice W where it avoids the fp32 carry (unless the caller's chunk_tokens says so, or H < 64).
+ * Returns 0 for invalid arguments.
  */
 size_t lce_workspace_size(int64_t N, int64_t H, int64_t V, int dtype, int with_backward,
                           int64_t chunk_tokens);

@@ -161,10 +161,17 @@ constexpr int64_t kFwdChunk = 16384;  // automatic forward chunk (a multiple of 
 // Beyond it the sum is carried in an fp32 accumulator of V x H in the workspace.
 int carry_chunks(int esz, int dtype) { return esz == 4 ? 0 : dtype == LCE_DTYPE_BF16 ? 4 : 9; }
 
+// Tokens of an automatic training chunk. Every chunk streams W twice and, after the first, reads and
+// writes dW once more, so few tokens are one chunk: up to kOneChunk of them and no more than H, so that
+// e (N x V) stays below W's own size (1000 tokens, H = 4096, V = 128256: 2.69 ms in one chunk, 4.04 in
+// three; 2048 tokens: 4.91 in one, 5.49 in two; for 131 MB of e more in each). More tokens make at
+// least two chunks of at most H, even ones where N / 2 is below H (a last chunk of a few tokens costs
+// nearly a whole one's dW).
+constexpr int64_t kOneChunk = 2048;
 int64_t auto_chunk(int64_t N, int64_t H) {
-  const int64_t half = cdiv(N, 2);
-  int64_t nc = std::min(H, half) / 64 * 64;
-  return std::max<int64_t>(64, nc);
+  if (N <= std::min(H, kOneChunk)) return N;
+  const int64_t half = round_up(cdiv(N, 2), 64);
+  return std::max<int64_t>(64, std::min(H / 64 * 64, half));
 }
 
 // The time of one contraction (microseconds, on 256 CUs), to choose between tiles and splits: the
@@ -235,9 +242,10 @@ bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_
 //
 // fp32: an entry's rounding error grows with the length of its running sum, V / splits terms, so Tile128's
 // finer grid may not take splits away: at least as many as fill the device with 256 x 256 tiles, up to
-// eight (8000 tokens, H = 512, V = 20000: dH is 1.4e-6 off in six splits, 0.6e-6 in 32).
-int fp32_min_splits(const Plan& p, int64_t kblocks) {
-  const int64_t tiles = tile_count(TILE_XB, p.H, p.nc);
+// eight (8000 tokens, H = 512, V = 20000: dH is 1.4e-6 off in six splits, 0.6e-6 in 32). A call whose
+// tokens are one chunk counts the tiles of half of them, as if it had been two.
+int fp32_min_splits(const Plan& p, int64_t kblocks, bool one_chunk) {
+  const int64_t tiles = tile_count(TILE_XB, p.H, one_chunk ? cdiv(p.nc, 2) : p.nc);
   double best = 1e300;
   int splits = 1;
   for (int s = 1; s <= std::min<int64_t>(kblocks, 8); ++s) {
@@ -246,10 +254,10 @@ int fp32_min_splits(const Plan& p, int64_t kblocks) {
   }
   return splits;
 }
-void plan_dh(Plan& p, int64_t kblocks) {
+void plan_dh(Plan& p, int64_t kblocks, bool one_chunk) {
   const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 ? TILE_256 : TILE_XB;
   const int64_t cap = std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
-  const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks) : 1;
+  const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks, one_chunk) : 1;
   double best = 1e300;
   for (const GemmTile t : {big, TILE_128, TILE_64}) {
     if (t == TILE_128 && p.esz == 2 && p.nc >= 1024) continue;
@@ -321,7 +329,7 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   if (backward) {
     const int64_t kbk = kTileBytes / p.esz;
     const int64_t kblocks = cdiv(V, kbk);
-    plan_dh(p, kblocks);
+    plan_dh(p, kblocks, chunk_tokens == 0 && p.chunks == 1);
     p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;
     p.tile_dw = dw_tile(nc, H, V, p.esz);
     p.dw_acc32 = p.esz == 2 && p.chunks > carry_chunks(p.esz, dtype);

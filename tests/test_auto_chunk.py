@@ -1,0 +1,30 @@
+"""The automatic chunk of a training call, by the library's own plan (no GPU): few tokens are one chunk,
+more make chunks that cover them without a last one of a few tokens, and e stays within its bound."""
+import pytest
+import torch
+
+from paper_2603_16428_amd import lce
+
+
+@pytest.mark.parametrize("N,H,dtype,chunk", [
+    (1, 64, "bf16", 1), (1000, 4096, "bf16", 1000), (2048, 2048, "bf16", 2048), (2048, 4096, "fp16", 2048),
+    (2049, 4096, "bf16", 1088), (3000, 4096, "bf16", 1536), (256, 256, "fp32", 256), (257, 256, "fp32", 192),
+    (129, 8, "bf16", 64), (1000, 768, "bf16", 512), (4096, 768, "bf16", 1024), (8192, 4096, "bf16", 4096)])
+def test_auto_chunk(N, H, dtype, chunk):
+    dt = {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype]
+    assert lce.auto_chunk_tokens(N, H, 5000, dt) == chunk
+    info = lce.plan_info(N, H, 5000, dt)
+    assert info["chunk_tokens"] == chunk and info["chunks"] == -(-N // chunk)
+    # e is no larger than W (twice W where that avoids the fp32 carry), but for the 64-token minimum.
+    assert chunk <= max(64, H, 2 * H if -(-N // H) > 4 and dtype == "bf16" else 0)
+
+
+@pytest.mark.parametrize("N,H,V", [(512, 512, 20000), (2000, 2048, 8000), (1024, 4096, 4096), (4096, 2048, 8192)])
+def test_fp32_dh_splits(N, H, V):
+    """fp32: a dH entry's running sum is no longer than with the splits that fill 256 CUs with 256 x 256
+    tiles of one chunk (of two halves, where the call is one chunk)."""
+    info = lce.plan_info(N, H, V, torch.float32)
+    tokens = info["chunk_tokens"] if info["chunks"] > 1 else -(-N // 2)
+    tiles = -(-tokens // 256) * -(-H // 256)
+    least = min(range(1, 9), key=lambda s: (round(-(-tiles * s // 256) / s + (0.03 * s if s > 1 else 0), 9), s))
+    assert info["dh_splits"] >= least
