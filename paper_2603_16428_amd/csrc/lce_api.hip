@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -201,20 +202,27 @@ GemmTile small_or_128(int esz, int64_t M, int64_t N, int64_t kt) {
 // logits^T = W . X_c^T: M = V, N = tokens, K = H. Of the large tiles, Tile128 overlaps its epilogues
 // with the other workgroup's main loop (V = 128256, H = 4096, 4096 tokens: 2.93 ms per chunk against
 // 3.16 for gemm_xb_kernel), but moves 1.5 times the operand bytes from L2: gemm_xb_kernel stays ahead
-// where the epilogue is a small part (H = 12288, V = 32768: 2.27 ms against 2.39) and where few
-// columns of tiles reuse W (1000 tokens, H = 4096, V = 128256: 0.82 ms against 0.87; at 2048 tokens
-// 1.64 against 1.58), if its tiles fill their rounds.
+// where the epilogue is a small part (H = 12288, V = 32768: 2.27 ms against 2.39; H = 5320, V = 62405, 2195 tokens: 1.33 against 1.37) and
+// where few columns of tiles reuse W (1000 tokens, H = 4096, V = 128256: 0.82 ms against 0.87; at 2048
+// tokens 1.64 against 1.58), unless its tiles fill their rounds worse (200 tokens, H = 4096, V = 32000:
+// 110 us against 89, but V = 43000, H = 8192: 220 against 245). Tile256 where its one round is nearly
+// two of Tile128 (200 tokens, H = 1176, V = 36623: 41 us against 45).
 GemmTile logits_tile(int64_t nc, int64_t H, int64_t V, int esz) {
-  const GemmTile t = small_or_128(esz, V, nc, cdiv(H * esz, kTileBytes));
+  const int64_t kt = cdiv(H * esz, kTileBytes);
+  const GemmTile t = small_or_128(esz, V, nc, kt);
   // One column of tiles is a stream of W: Tile128x64 leaves a quarter of Tile64's partials to combine
   // (24 tokens, H = 4096, V = 128256: 189 us a call against 209) where its workgroups fill the CUs
   // (V = 16384, H = 1024: 20.3 against 19.4).
   if (t == TILE_64 && esz == 2 && nc <= Tile128x64::kBN && V >= 250 * Tile128x64::kBM) return TILE_128x64;
   if (t == TILE_64 || esz == 4) return t;
+  // Tile128's workgroups by pairs on a CU, the last one perhaps alone.
+  const double rounds = (double)cdiv(tile_count(TILE_128, V, nc), 256), odd = rounds - 2.0 * std::floor(rounds / 2);
+  const double us_128 = (rounds - odd) / 2 * (2.0 + 1.56 * kt) + odd * (9.0 + 0.84 * kt);
   const int64_t xb = tile_count(TILE_XB, V, nc);
-  const bool filled = 10 * xb >= 9 * 256 * cdiv(xb, 256);
-  const bool long_k = H >= 8192 || (H >= 2048 && H >= 3 * nc && nc > 256);
-  return long_k && filled ? TILE_XB : TILE_128;
+  const double us_xb = gemm_us(TILE_XB, esz, xb, kt);
+  const bool long_k = H >= 5120 || (H >= 3072 && 2 * H >= 5 * nc);
+  if (long_k && us_xb <= 1.1 * us_128) return TILE_XB;
+  return xb <= 256 && us_xb - 3.0 <= us_128 && !long_k ? TILE_256 : TILE_128;
 }
 
 // dW = dZ_c^T . X_c: M = V, N = H, K = tokens. Tile128 (V = 128256, H = 4096, 4096 tokens: 3.09 ms
@@ -541,16 +549,10 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
 
     auto combine = [&](auto mode_c, const int* run_if) {
       KernelTimer t(T_OTHER, s);
-      auto launch = [&](auto tok) {
-        constexpr int TOK = decltype(tok)::value, MODE = decltype(mode_c)::value;
-        hipLaunchKernelGGL((combine_kernel<T, TOK, MODE>), dim3((unsigned)cdiv(rows, TOK)), dim3(kCombineThreads), 0, s,
-                           pmax, psum, p.ncp, (int)p.slices, rows, y + t0, ignore_index, tgt + t0, lse + t0, tl + t0,
-                           scale ? scale + t0 : nullptr, (const int*)nvalid, mean, ez, p.ez_kp, V,
-                           flags ? flags + c : nullptr, run_if);
-      };
-      // Few tokens: more blocks, and more threads per token.
-      if (rows <= 256) launch(std::integral_constant<int, 4>{});
-      else launch(std::integral_constant<int, 16>{});
+      hipLaunchKernelGGL((combine_kernel<T, decltype(mode_c)::value>), dim3((unsigned)cdiv(rows, kCombineTokens)),
+                         dim3(kCombineThreads), 0, s, pmax, psum, p.ncp, (int)p.slices, rows, y + t0, ignore_index,
+                         tgt + t0, lse + t0, tl + t0, scale ? scale + t0 : nullptr, (const int*)nvalid, mean, ez,
+                         p.ez_kp, V, flags ? flags + c : nullptr, run_if);
       return hipGetLastError();
     };
     using Tref = std::integral_constant<int, CMB_TREF>;

@@ -109,14 +109,13 @@ __device__ __forceinline__ void loss_sum_block(const float* __restrict__ tl, int
 
 // Row combine. For each token of the chunk: M = max_t m_t, lse = M + log sum_t s_t exp(m_t - M),
 // and the token loss lse - z_target (0 for ignored tokens). A block of 1024 threads takes
-// TOK = 16 tokens x 64 slice groups, or 4 x 256: thread (token j, group k) merges slices k, k +
-// groups, ... in increasing order (64- or 16-byte pieces of the slices' rows), then a wave's groups
-// are merged across its lanes and the 16 waves' sums by one thread per token, in a fixed order. The
-// partials are a few MB that come from HBM like the code itself (the GEMM before has streamed W
-// through every cache): what counts is how many threads share the chain of loads, and how few
-// instructions there are to fetch (hence a kernel per mode, and the sums unrolled only where loads
-// overlap). With 16 groups merging pairwise, 4096 tokens (V = 128256) took 17 us here, now 10; 24
-// tokens 20 us in two blocks, now 10 in six.
+// 16 tokens x 64 slice groups: thread (token j, group k) merges slices k, k + 64, ... in increasing
+// order (64-byte pieces of the slices' rows), then a wave's groups are merged across its lanes and
+// the 16 waves' sums by one thread per token, in a fixed order. The partials are a few MB that come
+// from HBM like the code itself (the GEMM before has streamed W through every cache): what counts is
+// how many threads share the chain of loads, and how few instructions there are to fetch (hence a
+// kernel per mode, and the sums unrolled only where loads overlap). With 16 groups merging pairwise,
+// 4096 tokens (V = 128256) took 17 us here, now 10, and 24 tokens 20 us, now 10.
 //
 // Backward, the per-token factor that the dH epilogue and the dW operand apply (scale_out):
 //   CMB_TREF  : e holds exp(z - z_target) for valid tokens (label in [0, V), not ignored), and the
@@ -134,8 +133,8 @@ __device__ __forceinline__ void loss_sum_block(const float* __restrict__ tl, int
 enum CombineMode { CMB_FORWARD = 0, CMB_TREF = 1, CMB_SLICE = 2 };
 constexpr float kTrefMaxSum = 1.1420073898e26f;  // exp(60)
 constexpr float kTrefMinSum = 0.5f;
-constexpr int kCombineThreads = 1024;
-template <typename T, int TOK, int MODE>
+constexpr int kCombineTokens = 16, kCombineThreads = 1024;
+template <typename T, int MODE>
 __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* __restrict__ pmax, const float* __restrict__ psum,
                                                       int64_t ldp, int slices, int rows,
                                                       const int64_t* __restrict__ y, int64_t ignore_index,
@@ -147,7 +146,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* _
                                                       int64_t KP, int64_t V, int* __restrict__ flag,
                                                       const int* __restrict__ run_if) {
   if (run_if != nullptr && *run_if == 0) return;
-  constexpr int kWaves = kCombineThreads / 64, kGroups = kCombineThreads / TOK;
+  constexpr int TOK = kCombineTokens, kWaves = kCombineThreads / 64, kGroups = kCombineThreads / TOK;
   __shared__ float sm[kWaves][TOK], ss[kWaves][TOK];
   const int t = threadIdx.x % TOK, grp = threadIdx.x / TOK;
   const int i = blockIdx.x * TOK + t;
@@ -157,8 +156,8 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* _
   constexpr bool kShared = MODE == CMB_TREF;
   float m = kShared ? 0.f : -INFINITY, s = 0.f;
   if (i < rows) {
-    // Sixteen slices' partials are requested before any is merged.
-    constexpr int kAhead = 16;
+    // Eight slices' partials are requested before any is merged.
+    constexpr int kAhead = 8;
 #pragma unroll 1
     for (int k0 = grp; k0 < slices; k0 += kGroups * kAhead) {
       float mk[kAhead], sk[kAhead];
@@ -166,13 +165,9 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* _
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
         const int k = k0 + kGroups * u;
-        const size_t o = (size_t)min(k, slices - 1) * ldp + i;
-        if constexpr (!kShared) {
-          mk[u] = pmax[o];
-          if (k >= slices) mk[u] = -INFINITY;
-        }
-        sk[u] = psum[o];
-        if (k >= slices) sk[u] = 0.f;
+        const size_t o = (size_t)k * ldp + i;
+        if constexpr (!kShared) mk[u] = k < slices ? pmax[o] : -INFINITY;
+        sk[u] = k < slices ? psum[o] : 0.f;
       }
       if constexpr (kShared) {
 #pragma unroll
