@@ -202,11 +202,12 @@ GemmTile small_or_128(int esz, int64_t M, int64_t N, int64_t kt) {
 // logits^T = W . X_c^T: M = V, N = tokens, K = H. Of the large tiles, Tile128 overlaps its epilogues
 // with the other workgroup's main loop (V = 128256, H = 4096, 4096 tokens: 2.93 ms per chunk against
 // 3.16 for gemm_xb_kernel), but moves 1.5 times the operand bytes from L2: gemm_xb_kernel stays ahead
-// where the epilogue is a small part (H = 12288, V = 32768: 2.27 ms against 2.39; H = 5320, V = 62405, 2195 tokens: 1.33 against 1.37) and
-// where few columns of tiles reuse W (1000 tokens, H = 4096, V = 128256: 0.82 ms against 0.87; at 2048
-// tokens 1.64 against 1.58), unless its tiles fill their rounds worse (200 tokens, H = 4096, V = 32000:
-// 110 us against 89, but V = 43000, H = 8192: 220 against 245). Tile256 where its one round is nearly
-// two of Tile128 (200 tokens, H = 1176, V = 36623: 41 us against 45).
+// where the epilogue is a small part (H = 12288, V = 32768: 2.27 ms against 2.39; H = 5320, V = 62405,
+// 2195 tokens: 1.33 against 1.37) and where few columns of tiles reuse W (1000 tokens, H = 4096,
+// V = 128256: 0.82 ms against 0.87; at 2048 tokens 1.64 against 1.58), unless its tiles fill their
+// rounds worse (200 tokens, H = 4096, V = 32000: 110 us against 89, but V = 43000, H = 8192: 220
+// against 245). Tile256 where its one round is nearly two of Tile128 (200 tokens, H = 1176, V = 36623:
+// 41 us against 45).
 GemmTile logits_tile(int64_t nc, int64_t H, int64_t V, int esz) {
   const int64_t kt = cdiv(H * esz, kTileBytes);
   const GemmTile t = small_or_128(esz, V, nc, kt);
@@ -1075,6 +1076,32 @@ lce_status_t lce_head_train_step(const void* hidden, const int64_t* labels, int6
                                  (lce::f16*)grad_hidden, (lce::f16*)grad_weight, loss, master, exp_avg, exp_avg_sq,
                                  (lce::f16*)grad_host, (lce::f16*)param_host, adam, step, vocab_blocks, n_threads,
                                  overlap != 0, (char*)workspace, s, timing);
+}
+
+// For the Python binding's autograd wrappers (not part of the C ABI): out[k] = in[k] * *factor for
+// `count` (1 to 3) device tensors of n[k] elements and one dtype; factor is a device float. All
+// pointers 16-byte aligned but factor's. Enqueued on `stream`.
+lce_status_t lce_internal_scale(const void* const* in, void* const* out, const int64_t* n, int count, int dtype,
+                                const float* factor, void* stream) {
+  if (!in || !out || !n || !factor || count < 1 || count > 3 || !lce::dtype_ok(dtype)) return LCE_ERR_INVALID_ARGUMENT;
+  lce::ScaleJobs j{};
+  j.factor = factor;
+  int64_t blocks = 0;
+  for (int k = 0; k < count; ++k) {
+    if (!in[k] || !out[k] || n[k] < 0 || ((uintptr_t)in[k] | (uintptr_t)out[k]) % 16 != 0) return LCE_ERR_INVALID_ARGUMENT;
+    j.in[k] = in[k];
+    j.out[k] = out[k];
+    j.n[k] = n[k];
+    j.blocks[k] = lce::cdiv(n[k] * (dtype == LCE_DTYPE_FP32 ? 4 : 2), lce::kScaleBlockBytes);
+    blocks += j.blocks[k];
+  }
+  if (blocks == 0) return LCE_OK;
+  if (blocks > INT32_MAX) return LCE_ERR_UNSUPPORTED;
+  auto kernel = dtype == LCE_DTYPE_BF16   ? lce::scale_kernel<lce::bf16>
+                : dtype == LCE_DTYPE_FP16 ? lce::scale_kernel<lce::f16>
+                                          : lce::scale_kernel<float>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, j);
+  return hipGetLastError() == hipSuccess ? LCE_OK : LCE_ERR_HIP;
 }
 
 lce_status_t lce_timing_enable(int enable) {

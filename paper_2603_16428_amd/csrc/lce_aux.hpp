@@ -371,6 +371,59 @@ void launch_split_reduce(const float* part, int splits, int64_t count, T* out, c
   }
 }
 
+// out[i] = in[i] * *factor in fp32, rounded once, for up to three tensors one after the other in one
+// launch (an autograd backward's gradients times the upstream one): 64 bytes per thread in four
+// 16-byte pieces, all requested before any is written. Bound by its 2 x n bytes of HBM: 131 + 8 MB of
+// bf16 take 44 us (6.3 TB/s), where torch's products of a bf16 tensor and an fp32 scalar took 217.
+// in and out 16-byte aligned.
+struct ScaleJobs {
+  const void* in[3];
+  void* out[3];
+  int64_t n[3];
+  int64_t blocks[3];
+  const float* factor;
+};
+constexpr int kScaleBlockBytes = 256 * 64;
+
+template <typename T>
+__global__ __launch_bounds__(256) void scale_kernel(const ScaleJobs j) {
+  constexpr int kVec = 16 / (int)sizeof(T);
+  typedef T vec_t __attribute__((ext_vector_type(kVec)));
+  int64_t b = blockIdx.x;
+  const void* src = j.in[0];
+  void* dst = j.out[0];
+  int64_t n = j.n[0];
+  if (b >= j.blocks[0]) {
+    b -= j.blocks[0];
+    const bool third = b >= j.blocks[1];
+    if (third) b -= j.blocks[1];
+    src = third ? j.in[2] : j.in[1];
+    dst = third ? j.out[2] : j.out[1];
+    n = third ? j.n[2] : j.n[1];
+  }
+  const float f = *j.factor;
+  const T* in = (const T*)src;
+  T* out = (T*)dst;
+  const int64_t i0 = b * (kScaleBlockBytes / (int)sizeof(T)) + (int64_t)threadIdx.x * kVec;
+  vec_t v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t i = i0 + u * 256 * kVec;
+    if (i + kVec <= n) v[u] = *(const vec_t*)(in + i);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t i = i0 + u * 256 * kVec;
+    if (i + kVec <= n) {
+#pragma unroll
+      for (int e = 0; e < kVec; ++e) v[u][e] = from_f32<T>(to_f32(v[u][e]) * f);
+      *(vec_t*)(out + i) = v[u];
+    } else {  // the last, partial piece
+      for (int64_t k = i; k < n; ++k) out[k] = from_f32<T>(to_f32(in[k]) * f);
+    }
+  }
+}
+
 // One launch for several independent bandwidth-bound jobs, each on its own consecutive range of
 // blocks of 256 threads (a job with 0 blocks is absent), in this order: prepare_block,
 // block_k_block, block_mn_block, dlogits_job, loss_sum_block (one block). Jobs in one launch touch

@@ -100,6 +100,9 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                                         vp, vp, vp, vp, vp, vp, ctypes.POINTER(AdamConfig), i64, ctypes.c_int,
                                         ctypes.c_int, ctypes.c_int, vp, sz, vp, ctypes.POINTER(HeadStepTiming)]
     lib.lce_head_train_step.restype = ctypes.c_int
+    lib.lce_internal_scale.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(i64), ctypes.c_int,
+                                       ctypes.c_int, vp, vp]
+    lib.lce_internal_scale.restype = ctypes.c_int
     lib.lce_timing_enable.argtypes = [ctypes.c_int]
     lib.lce_timing_enable.restype = ctypes.c_int
     lib.lce_timing_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64), ctypes.c_int]
@@ -241,6 +244,34 @@ def forward_backward(hidden, weight, labels, ignore_index: int = -100, reduction
     return loss[0], dH, dW
 
 
+def _scaled(grad_out, grads):
+    """The gradients times the upstream one, in new tensors.
+
+    One launch of the library for plain dense device tensors; whatever else autograd brings (a
+    graph or a tangent through grad_out, batched gradients, tracing, tensors that saved-tensor hooks
+    changed) goes through torch's own operators.
+    """
+    g = grad_out.to(torch.float32)
+    plain = (type(g) is torch.Tensor and g.numel() == 1 and not (torch.is_grad_enabled() and grad_out.requires_grad)
+             and torch._C._len_torch_dispatch_stack() == 0 and torch.autograd.forward_ad._current_level < 0)
+    dt = grads[0].dtype
+    # (Batched tensors, of torch.func or of is_grads_batched, have no storage.)
+    if not (plain and torch._C._has_storage(g) and dt in DTYPES and all(
+            type(t) is torch.Tensor and torch._C._has_storage(t) and t.is_cuda and t.device == g.device
+            and t.dtype == dt and t.is_contiguous() and t.data_ptr() % 16 == 0 for t in grads)):
+        return tuple((t * g).to(t.dtype) for t in grads)
+    outs = tuple(torch.empty_like(t) for t in grads)
+    n = len(grads)
+    with torch.cuda.device(g.device):
+        stream = ctypes.c_void_p(torch.cuda.current_stream(g.device).cuda_stream)
+        st = load_library().lce_internal_scale(
+            (ctypes.c_void_p * n)(*(t.data_ptr() for t in grads)), (ctypes.c_void_p * n)(*(t.data_ptr() for t in outs)),
+            (ctypes.c_int64 * n)(*(t.numel() for t in grads)), n, DTYPES[dt], _ptr(g), stream)
+    if st != LCE_OK:
+        raise LCEError(st, "lce_internal_scale")
+    return outs
+
+
 class LinearCrossEntropy(torch.autograd.Function):
     """loss = cross_entropy(hidden @ weight.T, labels) without the logits tensor.
 
@@ -259,9 +290,7 @@ class LinearCrossEntropy(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_out):
-        dH, dW = ctx.saved_tensors
-        g = grad_out.to(torch.float32)
-        return (dH * g).to(dH.dtype), (dW * g).to(dW.dtype), None, None, None
+        return (*_scaled(grad_out, ctx.saved_tensors), None, None, None)
 
 
 def linear_cross_entropy(hidden, weight, labels, ignore_index: int = -100, reduction: str = "mean"):
@@ -351,9 +380,7 @@ class RMSNormLinearCrossEntropy(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_out):
-        dh, dg, dW = ctx.saved_tensors
-        g = grad_out.to(torch.float32)
-        return (dh * g).to(dh.dtype), (dg * g).to(dg.dtype), (dW * g).to(dW.dtype), None, None, None, None
+        return (*_scaled(grad_out, ctx.saved_tensors), None, None, None, None)
 
 
 def rmsnorm_linear_cross_entropy(hidden, gamma, weight, labels, eps: float = 1e-5, ignore_index: int = -100,
