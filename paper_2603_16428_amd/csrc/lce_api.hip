@@ -730,7 +730,7 @@ lce_status_t run_rms(const RmsPlan& rp, const T* h, const T* gamma, const T* W, 
                      (const float*)dx, N, H, srow);
   hipLaunchKernelGGL((rmsnorm_backward_kernel<T>), dim3((unsigned)cdiv(H, 256), (unsigned)rp.row_blocks), dim3(256),
                      0, s, h, gamma, (const float*)r, (const float*)srow, (const float*)dx, dh, N, H, part);
-  hipLaunchKernelGGL((rmsnorm_gamma_reduce_kernel<T>), dim3((unsigned)cdiv(H, 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL((rmsnorm_gamma_reduce_kernel<T>), dim3((unsigned)cdiv(H, 64)), dim3(256), 0, s,
                      (const float*)part, (int)rp.row_blocks, H, dgamma);
   return hipGetLastError() == hipSuccess ? LCE_OK : LCE_ERR_HIP;
 }
