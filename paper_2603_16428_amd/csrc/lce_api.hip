@@ -244,10 +244,12 @@ bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_
 // counts as 1 us: at sizes where its few us matter the alternatives are as close.)
 // A split has to win by 5% (at nearly full grids the clock makes up for idle CUs), and its
 // partials stay below the size of W (or 64 MB). Of the 256 x 256 kernels, the eight waves of Tile256
-// are ahead at H > 1024 (H = 4096, V = 128256, 4096 tokens: 2.84 ms against 2.94), gemm_xb_kernel below
-// (H = 768: 0.34 against 0.36). 16-bit Tile128 is for few tokens, where its grid is the finer one; with
-// 2048 and more its operand traffic takes that back (H = 12288, V = 32768: 1.27 ms unsplit, Tile256
-// in two splits the same; H = 4096, V = 128256: 1.63 against 1.51).
+// are ahead (H = 4096, V = 128256, 4096 tokens: 2.84 ms against 2.94), gemm_xb_kernel only for narrow H
+// and long K (H = 768, V = 128256, 2048 tokens: 0.342 ms against 0.358). 16-bit Tile128 is for small
+// grids, which it cuts finer in fewer splits (H = 768, V = 50257, 1024 tokens: 75 us in ten splits
+// against 81 in Tile256's 21); with more tokens or columns its operand traffic takes that back
+// (H = 12288, V = 32768, 2048 tokens: 1.27 ms unsplit, Tile256 in two splits the same; H = 4096,
+// V = 128256, 2048 tokens: 1.63 against 1.51).
 //
 // fp32: an entry's rounding error grows with the length of its running sum, V / splits terms, so Tile128's
 // finer grid may not take splits away: at least as many as fill the device with 256 x 256 tiles, up to
@@ -264,12 +266,12 @@ int fp32_min_splits(const Plan& p, int64_t kblocks, bool one_chunk) {
   return splits;
 }
 void plan_dh(Plan& p, int64_t kblocks, bool one_chunk) {
-  const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 ? TILE_256 : TILE_XB;
+  const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 || p.V < 100000 ? TILE_256 : TILE_XB;
   const int64_t cap = std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
   const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks, one_chunk) : 1;
   double best = 1e300;
   for (const GemmTile t : {big, TILE_128, TILE_64}) {
-    if (t == TILE_128 && p.esz == 2 && p.nc >= 1024) continue;
+    if (t == TILE_128 && p.esz == 2 && p.nc >= 1024 && (p.H > 1024 || p.nc > 2048)) continue;
     const int64_t tiles = tile_count(t, p.H, p.nc);
     for (int64_t s = least; s <= std::min<int64_t>(kblocks, 128); ++s) {
       const int64_t part = s * p.nc * p.H * 4;
