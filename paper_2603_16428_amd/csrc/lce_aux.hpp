@@ -175,9 +175,11 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const float* _
       } else {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) mn = fmaxf(mn, mk[u]);
-        s *= __expf(m - mn);
+        // Partials of -inf logits alone (maximum -inf, sum 0) add nothing, also before any other.
+        const float ref = mn == -INFINITY ? 0.f : mn;
+        s *= __expf(m - ref);
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) s = fmaf(sk[u], __expf(mk[u] - mn), s);
+        for (int u = 0; u < kAhead; ++u) s = fmaf(sk[u], __expf(mk[u] - ref), s);
         m = mn;
       }
     }

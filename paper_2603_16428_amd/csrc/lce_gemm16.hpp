@@ -318,7 +318,7 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& g, f32x4 (&acc)[
           mx = fmaxf(mx, __shfl_xor(mx, 16));
           mx = fmaxf(mx, __shfl_xor(mx, 32));
           m_ref = mx;
-          ml = mx * kLog2e;
+          ml = mx == -INFINITY ? 0.f : mx * kLog2e;  // a partial of -inf logits alone sums to 0
         }
         // Every token block that holds a token of the chunk is written whole. This lane's chunk of a
         // K-quad is in K-pair l/32, half (l/16)%2 of column l%16 (+ 16 for odd j).

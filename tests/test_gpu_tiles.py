@@ -50,3 +50,17 @@ def test_forward_in_every_tile(lce, N, H, V, dtype):  # noqa: F811
     # fp32 sums of H products and V exponentials; the bars of the reduced loss hold for every token.
     assert np.abs(loss.cpu().numpy() - ref["loss"]).max() <= TOL[dtype][0] * np.abs(ref["loss"]).max()
     assert np.abs(lse.cpu().numpy() - ref["lse"]).max() <= TOL[dtype][0] * np.abs(ref["lse"]).max()
+
+
+@pytest.mark.parametrize("N,H,V,lo,hi", [(65, 72, 3001, 0, 40), (65, 72, 3001, 64, 96), (64, 64, 40000, 128, 256)])
+def test_forward_with_slices_of_minus_inf(lce, N, H, V, lo, hi):  # noqa: F811
+    """Ids whose logits are -inf add nothing to a token's sum, also where they fill a whole partial (64 x 64 and
+    128 x 64 tiles: 32 and 128 ids): the other ids' losses, of the oracle without them."""
+    d = workloads.make_inputs("llama3_8b", seed=33, N=N, H=H, V=V, dtype="bf16")
+    hidden = d["hidden"].abs() + 0.01
+    weight, labels = d["weight"].clone(), torch.arange(N) + hi
+    ref = oracle.forward(hidden, torch.cat((weight[:lo], weight[hi:])), labels - (hi - lo), -100, "none")
+    weight[lo:hi] = -float("inf")
+    loss, lse = lce.forward(hidden.cuda(), weight.cuda(), labels.cuda(), -100, "none", return_lse=True)
+    assert np.abs(loss.cpu().numpy() - ref["loss"]).max() <= TOL["bf16"][0] * np.abs(ref["loss"]).max()
+    assert np.abs(lse.cpu().numpy() - ref["lse"]).max() <= TOL["bf16"][0] * np.abs(ref["lse"]).max()
