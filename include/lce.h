@@ -156,7 +156,8 @@ lce_status_t lce_forward(const void* hidden, const void* weight, const int64_t* 
  *   - Scratch is a static device array of LCE_NO_ALLOC_SCRATCH_BYTES (64 MiB) inside the library,
  *     one per device, held from the library's first use on that device until the process ends.
  *     The call picks the largest chunk of tokens whose workspace fits it (the results do not depend
- *     on the chunk) and returns LCE_ERR_WORKSPACE_TOO_SMALL, before anything is enqueued, when even
+ *     on the chunk; where 64 tokens fit only with partial sums of 128 vocabulary rows instead of 32,
+ *     V in the millions, they may differ from lce_forward's in the last bits) and returns LCE_ERR_WORKSPACE_TOO_SMALL, before anything is enqueued, when even
  *     64 tokens per chunk need more (the per-token part is 12 N bytes: N up to about 5 million at
  *     H = 4096, V = 128256).
  *   - The array is shared by every call on a device and keeps the last call's contents (nothing in
