@@ -244,21 +244,28 @@ def forward_backward(hidden, weight, labels, ignore_index: int = -100, reduction
     return loss[0], dH, dW
 
 
+def _bytes_are_values(t) -> bool:
+    """Whether t's values are what its memory holds: not a lazily negated view (an imaginary part of a
+    conjugate), whose bytes have the other sign, nor a zero tensor, which has no memory at all."""
+    return not t.is_neg() and (t.data_ptr() != 0 or t.numel() == 0)
+
+
 def _scaled(grad_out, grads):
     """The gradients times the upstream one, in new tensors.
 
     One launch of the library for plain dense device tensors; whatever else autograd brings (a
-    graph or a tangent through grad_out, batched gradients, tracing, tensors that saved-tensor hooks
-    changed) goes through torch's own operators.
+    graph or a tangent through grad_out, batched gradients, tracing, lazily negated or zero tensors,
+    tensors that saved-tensor hooks changed) goes through torch's own operators.
     """
     g = grad_out.to(torch.float32)
     plain = (type(g) is torch.Tensor and g.numel() == 1 and not (torch.is_grad_enabled() and grad_out.requires_grad)
              and torch._C._len_torch_dispatch_stack() == 0 and torch.autograd.forward_ad._current_level < 0)
     dt = grads[0].dtype
     # (Batched tensors, of torch.func or of is_grads_batched, have no storage.)
-    if not (plain and torch._C._has_storage(g) and dt in DTYPES and all(
-            type(t) is torch.Tensor and torch._C._has_storage(t) and t.is_cuda and t.device == g.device
-            and t.dtype == dt and t.is_contiguous() and t.data_ptr() % 16 == 0 for t in grads)):
+    if not (plain and torch._C._has_storage(g) and _bytes_are_values(g) and dt in DTYPES and all(
+            type(t) is torch.Tensor and torch._C._has_storage(t) and _bytes_are_values(t) and t.is_cuda
+            and t.device == g.device and t.dtype == dt and t.is_contiguous() and t.data_ptr() % 16 == 0
+            for t in grads)):
         return tuple((t * g).to(t.dtype) for t in grads)
     outs = tuple(torch.empty_like(t) for t in grads)
     n = len(grads)

@@ -64,6 +64,25 @@ def test_other_upstream_gradients(lce):
     assert torch.isfinite(back) and abs(back.item() - one[0].float().sum().item()) <= 1e-2 * one[0].float().abs().sum().item()
 
 
+def test_lazily_negated_and_zero_gradients(lce):
+    """A negative bit (the imaginary part of a conjugate) and a zero tensor have other values than the
+    memory that their pointers name, as upstream gradients and as tensors that a saved-tensor hook gives."""
+    X, W, y = _leaves(lce, "bf16")
+    loss = lce.linear_cross_entropy(X, W, y)
+    want = torch.autograd.grad(loss, (X, W), torch.tensor(-2.0, device="cuda"), retain_graph=True)
+    neg = torch.complex(torch.tensor(0.0), torch.tensor(2.0)).cuda().conj().imag
+    assert neg.is_neg() and neg.item() == -2.0
+    for got, w in zip(torch.autograd.grad(loss, (X, W), neg, retain_graph=True), want):
+        assert torch.equal(got, w)
+    zero = torch._efficientzerotensor((), device="cuda")
+    for got in torch.autograd.grad(loss, (X, W), zero, retain_graph=True):
+        assert not got.any()
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, torch._neg_view):
+        hooked = lce.linear_cross_entropy(X, W, y)
+    for got, w in zip(torch.autograd.grad(hooked, (X, W), torch.tensor(2.0, device="cuda")), want):
+        assert torch.equal(got, w)
+
+
 def test_rmsnorm_wrapper(lce):
     d = workloads.make_rmsnorm_inputs("llama3_8b", seed=3, N=70, H=72, V=1031)
     h, g, W = (d[k].cuda().requires_grad_() for k in ("hidden", "gamma", "weight"))
