@@ -244,10 +244,27 @@ def forward_backward(hidden, weight, labels, ignore_index: int = -100, reduction
     return loss[0], dH, dW
 
 
+# How many dispatch modes (tracing, counting, fake tensors) are active. None where this torch does not say:
+# then no tensor counts as plain, and torch's operators do the scaling.
+_dispatch_modes = getattr(torch._C, "_len_torch_dispatch_stack", None)
+
+
 def _bytes_are_values(t) -> bool:
-    """Whether t's values are what its memory holds: not a lazily negated view (an imaginary part of a
+    """Whether t is a plain tensor whose values are what its memory holds: not a subclass's or a batched one
+    (of torch.func or of is_grads_batched: no storage), not a lazily negated view (an imaginary part of a
     conjugate), whose bytes have the other sign, nor a zero tensor, which has no memory at all."""
+    if type(t) is not torch.Tensor or t.layout != torch.strided:
+        return False
+    try:
+        t.untyped_storage()
+    except (NotImplementedError, RuntimeError):
+        return False
     return not t.is_neg() and (t.data_ptr() != 0 or t.numel() == 0)
+
+
+def _differentiated(t) -> bool:
+    """Whether autograd follows t here: a graph (double backward), or a forward-mode tangent."""
+    return (torch.is_grad_enabled() and t.requires_grad) or torch.autograd.forward_ad.unpack_dual(t).tangent is not None
 
 
 def _scaled(grad_out, grads):
@@ -258,13 +275,11 @@ def _scaled(grad_out, grads):
     tensors that saved-tensor hooks changed) goes through torch's own operators.
     """
     g = grad_out.to(torch.float32)
-    plain = (type(g) is torch.Tensor and g.numel() == 1 and not (torch.is_grad_enabled() and grad_out.requires_grad)
-             and torch._C._len_torch_dispatch_stack() == 0 and torch.autograd.forward_ad._current_level < 0)
+    plain = (_dispatch_modes is not None and _dispatch_modes() == 0
+             and all(_bytes_are_values(t) and not _differentiated(t) for t in (g, *grads)) and g.numel() == 1)
     dt = grads[0].dtype
-    # (Batched tensors, of torch.func or of is_grads_batched, have no storage.)
-    if not (plain and torch._C._has_storage(g) and _bytes_are_values(g) and dt in DTYPES and all(
-            type(t) is torch.Tensor and torch._C._has_storage(t) and _bytes_are_values(t) and t.is_cuda
-            and t.device == g.device and t.dtype == dt and t.is_contiguous() and t.data_ptr() % 16 == 0
+    if not (plain and dt in DTYPES and all(
+            t.is_cuda and t.device == g.device and t.dtype == dt and t.is_contiguous() and t.data_ptr() % 16 == 0
             for t in grads)):
         return tuple((t * g).to(t.dtype) for t in grads)
     outs = tuple(torch.empty_like(t) for t in grads)
