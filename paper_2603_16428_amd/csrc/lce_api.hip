@@ -175,6 +175,13 @@ int64_t auto_chunk(int64_t N, int64_t H) {
   return std::max<int64_t>(64, std::min(H / 64 * 64, half));
 }
 
+// fp32 only: the tokens that an automatic call's sums and splits are sized for, half of the tokens rounded
+// down to 64 and at most H. A rounding error grows with the length of its running sum, so neither one
+// chunk instead of several nor N / 2 rounded up may make the sums longer than at these.
+int64_t fp32_chunk(int64_t N, int64_t H) {
+  return std::min(N, std::max<int64_t>(64, std::min(H, cdiv(N, 2)) / 64 * 64));
+}
+
 // The time of one contraction (microseconds, on 256 CUs), to choose between tiles and splits: the
 // busiest CU's tiles one after the other, each a fixed part and `kt` K-tiles of 128 bytes. Measured
 // over N = 64 .. 4096, H = 256 .. 12288, V = 4096 .. 128256. 16-bit, a K-tile: 1.5 us for 256 x 256
@@ -252,11 +259,12 @@ bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_
 // V = 128256, 2048 tokens: 1.63 against 1.51).
 //
 // fp32: an entry's rounding error grows with the length of its running sum, V / splits terms, so Tile128's
-// finer grid may not take splits away: at least as many as fill the device with 256 x 256 tiles, up to
-// eight (8000 tokens, H = 512, V = 20000: dH is 1.4e-6 off in six splits, 0.6e-6 in 32). A call whose
-// tokens are one chunk counts the tiles of half of them, as if it had been two.
-int fp32_min_splits(const Plan& p, int64_t kblocks, bool one_chunk) {
-  const int64_t tiles = tile_count(TILE_XB, p.H, one_chunk ? cdiv(p.nc, 2) : p.nc);
+// finer grid and larger chunks may not take splits away: at least as many as fill the device with 256 x 256
+// tiles of `tokens` tokens (fp32_chunk of an automatic call), up to eight (8000 tokens, H = 512, V = 20000:
+// dH is 1.4e-6 off in six splits, 0.6e-6 in 32; 11786 tokens, H = 7896, V = 12703: 1.2e-6 in five, 2.8e-6
+// in one).
+int fp32_min_splits(const Plan& p, int64_t kblocks, int64_t tokens) {
+  const int64_t tiles = tile_count(TILE_XB, p.H, tokens);
   double best = 1e300;
   int splits = 1;
   for (int s = 1; s <= std::min<int64_t>(kblocks, 8); ++s) {
@@ -265,10 +273,10 @@ int fp32_min_splits(const Plan& p, int64_t kblocks, bool one_chunk) {
   }
   return splits;
 }
-void plan_dh(Plan& p, int64_t kblocks, bool one_chunk) {
+void plan_dh(Plan& p, int64_t kblocks, int64_t fp32_tokens) {
   const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 || p.V < 100000 ? TILE_256 : TILE_XB;
   const int64_t cap = std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
-  const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks, one_chunk) : 1;
+  const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks, fp32_tokens) : 1;
   double best = 1e300;
   for (const GemmTile t : {big, TILE_128, TILE_64}) {
     if (t == TILE_128 && p.esz == 2 && p.nc >= 1024 && (p.H > 1024 || p.nc > 2048)) continue;
@@ -340,7 +348,7 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   if (backward) {
     const int64_t kbk = kTileBytes / p.esz;
     const int64_t kblocks = cdiv(V, kbk);
-    plan_dh(p, kblocks, chunk_tokens == 0 && p.chunks == 1);
+    plan_dh(p, kblocks, chunk_tokens == 0 ? fp32_chunk(N, H) : nc);
     p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;
     p.tile_dw = dw_tile(nc, H, V, p.esz);
     p.dw_acc32 = p.esz == 2 && p.chunks > carry_chunks(p.esz, dtype);

@@ -1,5 +1,8 @@
 """The automatic chunk of a training call, by the library's own plan (no GPU): few tokens are one chunk,
 more make chunks that cover them without a last one of a few tokens, and e stays within its bound."""
+import math
+import random
+
 import pytest
 import torch
 
@@ -19,12 +22,28 @@ def test_auto_chunk(N, H, dtype, chunk):
     assert chunk <= max(64, H, 2 * H if -(-N // H) > 4 and dtype == "bf16" else 0)
 
 
-@pytest.mark.parametrize("N,H,V", [(512, 512, 20000), (2000, 2048, 8000), (1024, 4096, 4096), (4096, 2048, 8192)])
+def _fp32_chunk(N, H):
+    """Half of the tokens rounded down to 64, at most H: what an fp32 call's sums are sized for."""
+    return min(N, max(64, min(H, -(-N // 2)) // 64 * 64))
+
+
+def _fp32_splits(N, H):
+    """The splits (1 to 8) that fill 256 CUs best with 256 x 256 tiles of such a chunk."""
+    tiles = -(-_fp32_chunk(N, H) // 256) * -(-H // 256)
+    return min(range(1, 9), key=lambda s: (round(-(-tiles * s // 256) / s + (0.03 * s if s > 1 else 0), 9), s))
+
+
+# The last three: N / 2 rounded up to 64 is one row of tiles more than rounded down.
+@pytest.mark.parametrize("N,H,V", [(512, 512, 20000), (2000, 2048, 8000), (1024, 4096, 4096), (4096, 2048, 8192),
+                                   (11786, 7896, 12703), (10287, 5664, 9125), (9269, 6248, 13225)])
 def test_fp32_dh_splits(N, H, V):
     """fp32: a dH entry's running sum is no longer than with the splits that fill 256 CUs with 256 x 256
-    tiles of one chunk (of two halves, where the call is one chunk)."""
-    info = lce.plan_info(N, H, V, torch.float32)
-    tokens = info["chunk_tokens"] if info["chunks"] > 1 else -(-N // 2)
-    tiles = -(-tokens // 256) * -(-H // 256)
-    least = min(range(1, 9), key=lambda s: (round(-(-tiles * s // 256) / s + (0.03 * s if s > 1 else 0), 9), s))
-    assert info["dh_splits"] >= least
+    tiles of half the tokens, whatever the chunk."""
+    assert lce.plan_info(N, H, V, torch.float32)["dh_splits"] >= _fp32_splits(N, H)
+
+
+def test_fp32_dh_splits_over_the_range():
+    rng = random.Random(7)
+    for _ in range(2000):
+        N, H, V = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((64, 16384), (32, 1536), (4096, 152064)))
+        assert lce.plan_info(N, 8 * H, V, torch.float32)["dh_splits"] >= _fp32_splits(N, 8 * H), (N, 8 * H, V)
