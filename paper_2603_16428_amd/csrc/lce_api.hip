@@ -120,6 +120,7 @@ struct Plan {
   int64_t slices = 0;
   int dh_splits = 1;
   int64_t dh_kps = 0;             // K (vocabulary) per dH split, multiple of the K-tile
+  int64_t dw_run = 0;             // tokens per running sum of dW, multiple of the K-tile
   // dW's running sum over chunks in an fp32 accumulator instead of dW's own 16-bit type (more
   // chunks than carry_chunks() allows for the type).
   bool dw_acc32 = false;
@@ -348,7 +349,9 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   if (backward) {
     const int64_t kbk = kTileBytes / p.esz;
     const int64_t kblocks = cdiv(V, kbk);
-    plan_dh(p, kblocks, chunk_tokens == 0 ? fp32_chunk(N, H) : nc);
+    const int64_t fp32_tokens = chunk_tokens == 0 ? fp32_chunk(N, H) : nc;
+    plan_dh(p, kblocks, fp32_tokens);
+    p.dw_run = round_up(p.esz == 4 ? cdiv(nc, cdiv(nc, fp32_tokens)) : nc, kbk);
     p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;
     p.tile_dw = dw_tile(nc, H, V, p.esz);
     p.dw_acc32 = p.esz == 2 && p.chunks > carry_chunks(p.esz, dtype);
@@ -645,7 +648,7 @@ lce_status_t run(const Plan& p, const T* X, const T* W, const int64_t* y, int64_
     gw.A = ez; gw.lda = p.ez_kp; gw.M = (int)V;
     gw.B = xm; gw.ldb = p.xm_kp; gw.N = (int)H;
     gw.K = rows;
-    gw.splits = 1; gw.k_per_split = (int)round_up(rows, kTileBytes / p.esz);
+    gw.splits = 1; gw.k_per_split = (int)p.dw_run;
     gw.out = dW; gw.ldo = H;
     const bool last = c == p.chunks - 1;
     gw.mode = c == 0 ? DW_STORE : DW_ACCUMULATE;

@@ -287,7 +287,7 @@ struct Operand16 {
 // the sub-tile; with it (DW) row 16 i + l%16, column 16 j + 4 (l/16) + r.
 template <typename T, int EPI, bool PRELOADED, int NI, int NJ>
 __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& g, f32x4 (&acc)[NI][NJ], int mw, int nw, int split,
-                                                int n0, const char* refs_lds) {
+                                                int n0, const char* refs_lds, bool later_run) {
   constexpr int kEsz = (int)sizeof(T);
   const int lane = lane_id();
   const int l16 = lane & 15, grp = lane >> 4;
@@ -399,8 +399,8 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& g, f32x4 (&acc)[
     const float sc = dz_epilogue_scale<T>(g.n_valid, g.mean);
     const bool acc32 = g.mode >= DW_ACC32_FIRST;
     // fp32 values land directly: acc32 (+)= sc C, at the last chunk dW = acc32 + sc C; fp32 dW itself
-    // (no preload) likewise in one buffer.
-    const bool read = acc32 ? g.mode != DW_ACC32_FIRST : g.mode == DW_ACCUMULATE;
+    // (no preload) likewise in one buffer, also from one run of the tokens to the next.
+    const bool read = acc32 ? g.mode != DW_ACC32_FIRST : g.mode == DW_ACCUMULATE || later_run;
     const bool last = g.mode == DW_ACC32_LAST;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -440,8 +440,9 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& g, f32x4 (&acc)[
 // registers, four K-quads of fragments, three ahead. A K-tile is four sections, K-quad p/2 by half p%2
 // of the wave's row blocks; each section's A fragments are read during the one before it, and it issues
 // a quarter of A's K-tile three ahead and half of B's fragments three K-quads ahead.
+// run: the run-th k_per_split of K (fp32 dW, see gemm_xs_kernel; else 0).
 template <typename T, int EPI, int AL, bool KCHECK, typename C>
-__device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, char* smem) {
+__device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, int run, char* smem) {
   constexpr int kEsz = (int)sizeof(T);
   constexpr int kBK = kTileBytes / kEsz;
   constexpr bool kSwap = EPI == EPI_DW;
@@ -460,7 +461,7 @@ __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, char* s
   const int split = rest / g.tiles_n;
   const int m0 = tm * C::kBM, n0 = tn * C::kBN;
   const int mw = m0 + wm * 16 * NI, nw = n0 + wn * 16 * NJ;
-  const int kb = split * g.k_per_split;
+  const int kb = (split + run) * g.k_per_split;
   const int ke = min(g.K, kb + g.k_per_split);
 
   using Op = Operand16<T, AL, C>;
@@ -660,14 +661,26 @@ __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, char* s
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     sync_frags();
   }
-  gemm_epilogue16<T, EPI, kPreload>(g, acc, mw, nw, split, n0, smem + kXbASlots * C::kSlot);
+  gemm_epilogue16<T, EPI, kPreload>(g, acc, mw, nw, split, n0, smem + kXbASlots * C::kSlot, run > 0);
 }
+
+// fp32 dW in runs of k_per_split tokens, one after the other, each added to the sum of the earlier ones in
+// dW: an entry's rounding error grows with the length of its running sum (2048 tokens, H = 2048: 7.7e-7 in
+// one run, 5.5e-7 in two of half of them).
 
 template <typename T, int EPI, int AL, bool KCHECK, typename C>
 __global__ __launch_bounds__(C::kThreads, C::kBM == 256 ? 1 : C::kBM == 128 ? 2 : 4) void gemm_xs_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   if (g.run_if != nullptr && __builtin_amdgcn_readfirstlane(*g.run_if) == 0) return;
-  gemm_xs_tile<T, EPI, AL, KCHECK, C>(g, blockIdx.x, smem);
+  if constexpr (EPI == EPI_DW && sizeof(T) == 4) {
+    for (int run = 0; run * g.k_per_split < g.K; ++run) {
+      // Every wave is done with the ring, and the tile's stores no longer count in vmcnt.
+      if (run > 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      gemm_xs_tile<T, EPI, AL, KCHECK, C>(g, blockIdx.x, run, smem);
+    }
+  } else {
+    gemm_xs_tile<T, EPI, AL, KCHECK, C>(g, blockIdx.x, 0, smem);
+  }
 }
 
 }  // namespace lce
