@@ -176,10 +176,11 @@ int64_t auto_chunk(int64_t N, int64_t H) {
   return std::max<int64_t>(64, std::min(H / 64 * 64, half));
 }
 
-// fp32 only: the tokens that an automatic call's sums and splits are sized for, half of the tokens rounded
-// down to 64 and at most H. A rounding error grows with the length of its running sum, so neither one
-// chunk instead of several nor N / 2 rounded up may make the sums longer than at these.
-int64_t fp32_chunk(int64_t N, int64_t H) {
+// Half of the tokens rounded down to 64, at most H. fp32 sums and splits of an automatic call are sized for
+// these: a rounding error grows with the length of its running sum, so neither one chunk instead of several
+// nor N / 2 rounded up may make the sums longer. And automatic chunks of rows so wide that the 32-bit limit
+// of a chunk's blocked copies would refuse auto_chunk's are of these.
+int64_t half_chunk(int64_t N, int64_t H) {
   return std::min(N, std::max<int64_t>(64, std::min(H, cdiv(N, 2)) / 64 * 64));
 }
 
@@ -261,7 +262,7 @@ bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_
 //
 // fp32: an entry's rounding error grows with the length of its running sum, V / splits terms, so Tile128's
 // finer grid and larger chunks may not take splits away: at least as many as fill the device with 256 x 256
-// tiles of `tokens` tokens (fp32_chunk of an automatic call), up to eight (8000 tokens, H = 512, V = 20000:
+// tiles of `tokens` tokens (half_chunk of an automatic call), up to eight (8000 tokens, H = 512, V = 20000:
 // dH is 1.4e-6 off in six splits, 0.6e-6 in 32; 11786 tokens, H = 7896, V = 12703: 1.2e-6 in five, 2.8e-6
 // in one).
 int fp32_min_splits(const Plan& p, int64_t kblocks, int64_t tokens) {
@@ -305,20 +306,27 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   p.dtype = dtype;
   p.tref = backward && dtype != LCE_DTYPE_FP16;
   if (H % (16 / p.esz) != 0) return LCE_ERR_UNSUPPORTED;
+  const int64_t lim = (int64_t(1) << 31) - 1;
   // Automatic chunks: a training step keeps one chunk's e/dZ, so its chunks stay small; a forward
   // call keeps only per-slice partials (N V / 16 bytes), so it takes up to 16384 tokens at once
   // (one launch of the logits GEMM instead of several, each with a partly empty last wave).
+  auto copies_fit = [&](int64_t tokens) {  // 32-bit limits of a chunk's two blocked copies of X
+    if (tokens > lim || H > lim) return false;
+    const int64_t xk = round_up(tokens, 64) / 32 * (round_up(H * p.esz, kTileBytes) / 32);
+    const int64_t xm = cdiv(H, 32) * (round_up(round_up(tokens, 64) * p.esz, kTileBytes) / 32);
+    return std::max(xk, xm) <= lim / 1024;
+  };
   int64_t nc = chunk_tokens != 0 ? chunk_tokens
-               : backward      ? auto_chunk(N, H)
+               : backward      ? (copies_fit(auto_chunk(N, H)) ? auto_chunk(N, H) : half_chunk(N, H))
                : N <= kFwdChunk ? N
                                 : std::max(auto_chunk(N, H), kFwdChunk);
   // An automatic backward chunk grows, when that keeps the chunk count within the type's carry
   // limit, up to 2 H tokens: its e buffer then grows by less than the fp32 accumulator (V x H x 4
   // bytes) it makes unnecessary.
   if (chunk_tokens == 0 && backward) {
-    const int lim = carry_chunks(p.esz, dtype);
-    if (lim > 0 && cdiv(N, nc) > lim) {
-      const int64_t grown = round_up(cdiv(N, lim), 64);
+    const int carry = carry_chunks(p.esz, dtype);
+    if (carry > 0 && cdiv(N, nc) > carry) {
+      const int64_t grown = round_up(cdiv(N, carry), 64);
       if (grown <= 2 * H) nc = grown;
     }
   }
@@ -334,7 +342,6 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   p.slices = cdiv(V, p.slice_rows);
   // 32-bit limits: buffer ranges of one 256-row operand slice (and of four column blocks of a
   // blocked operand), and int tile/element indices.
-  const int64_t lim = (int64_t(1) << 31) - 1;
   const int64_t maxpitch = std::max({H, round_up(V, kTile)});
   if ((int64_t)kTile * maxpitch * p.esz > lim || N > lim / 2 || V > lim / 2 || H > lim / 2) return LCE_ERR_UNSUPPORTED;
   if (cdiv(V, kTile) * cdiv(H, kTile) > lim / 16) return LCE_ERR_UNSUPPORTED;
@@ -342,14 +349,14 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   p.xk_kp = round_up(H * p.esz, kTileBytes) / 32;
   p.xm_nb = cdiv(H, 32);
   p.xm_kp = round_up(p.ncp * p.esz, kTileBytes) / 32;
-  if (p.xk_nb * p.xk_kp * 1024 > lim || p.xm_nb * p.xm_kp * 1024 > lim) return LCE_ERR_UNSUPPORTED;
+  if (!copies_fit(nc)) return LCE_ERR_UNSUPPORTED;
   p.ez_nb = p.ncp / 32;
   p.ez_kp = round_up(V, kTile) * p.esz / 32;
 
   if (backward) {
     const int64_t kbk = kTileBytes / p.esz;
     const int64_t kblocks = cdiv(V, kbk);
-    const int64_t fp32_tokens = chunk_tokens == 0 ? fp32_chunk(N, H) : nc;
+    const int64_t fp32_tokens = chunk_tokens == 0 ? half_chunk(N, H) : nc;
     plan_dh(p, kblocks, fp32_tokens);
     p.dw_run = round_up(p.esz == 4 ? cdiv(nc, cdiv(nc, fp32_tokens)) : nc, kbk);
     p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;

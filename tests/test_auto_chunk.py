@@ -47,3 +47,13 @@ def test_fp32_dh_splits_over_the_range():
     for _ in range(2000):
         N, H, V = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((64, 16384), (32, 1536), (4096, 152064)))
         assert lce.plan_info(N, 8 * H, V, torch.float32)["dh_splits"] >= _fp32_splits(N, 8 * H), (N, 8 * H, V)
+
+
+@pytest.mark.parametrize("N,H,V,dtype,chunk", [
+    (1652, 1159040, 60913, "bf16", 768), (380, 1958364, 56, "fp32", 128), (625, 3319736, 7, "fp16", 256),
+    (1100, 1048576, 1000, "bf16", 512), (65, 4000000, 5, "bf16", 65)])
+def test_wide_rows_are_accepted(N, H, V, dtype, chunk):
+    """Rows so wide that one chunk's blocked copies would pass 2^31 bytes: chunks of half the tokens."""
+    dt = {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype]
+    assert lce.plan_info(N, H, V, dt)["chunk_tokens"] == chunk
+    assert lce.workspace_size(N, H, V, dt) > 0
