@@ -316,10 +316,11 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
     const int64_t xm = cdiv(H, 32) * (round_up(round_up(tokens, 64) * p.esz, kTileBytes) / 32);
     return std::max(xk, xm) <= lim / 1024;
   };
+  const int64_t training = copies_fit(auto_chunk(N, H)) ? auto_chunk(N, H) : half_chunk(N, H);
   int64_t nc = chunk_tokens != 0 ? chunk_tokens
-               : backward      ? (copies_fit(auto_chunk(N, H)) ? auto_chunk(N, H) : half_chunk(N, H))
+               : backward      ? training
                : N <= kFwdChunk ? N
-                                : std::max(auto_chunk(N, H), kFwdChunk);
+                                : std::max(training, kFwdChunk);
   // An automatic backward chunk grows, when that keeps the chunk count within the type's carry
   // limit, up to 2 H tokens: its e buffer then grows by less than the fp32 accumulator (V x H x 4
   // bytes) it makes unnecessary.

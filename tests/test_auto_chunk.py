@@ -57,3 +57,9 @@ def test_wide_rows_are_accepted(N, H, V, dtype, chunk):
     dt = {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype]
     assert lce.plan_info(N, H, V, dt)["chunk_tokens"] == chunk
     assert lce.workspace_size(N, H, V, dt) > 0
+
+
+def test_wide_rows_are_accepted_forward_only():
+    """More than 16384 tokens in chunks of half of them, where the half rounded up would not fit the limit."""
+    info = lce.plan_info(40068, 26744, 56849, torch.float32, with_backward=False)
+    assert info["chunk_tokens"] == 20032 and info["chunks"] == 3
