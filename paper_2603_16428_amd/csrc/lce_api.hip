@@ -1099,6 +1099,20 @@ lce_status_t lce_head_train_step(const void* hidden, const int64_t* labels, int6
                                  overlap != 0, (char*)workspace, s, timing);
 }
 
+// For tests (not part of the C ABI): the tiles (GemmTile) of a call's logits, dH and dW, the latter two -1
+// without a backward.
+lce_status_t lce_internal_tiles(int64_t N, int64_t H, int64_t V, int dtype, int with_backward, int64_t chunk_tokens,
+                                int32_t* tiles) {
+  if (!tiles) return LCE_ERR_INVALID_ARGUMENT;
+  lce::Plan p;
+  const lce_status_t st = lce::make_plan(N, H, V, dtype, with_backward != 0, chunk_tokens, p);
+  if (st != LCE_OK) return st;
+  tiles[0] = p.tile_lg;
+  tiles[1] = p.backward ? p.tile_dh : -1;
+  tiles[2] = p.backward ? p.tile_dw : -1;
+  return LCE_OK;
+}
+
 // For the Python binding's autograd wrappers (not part of the C ABI): out[k] = in[k] * *factor for
 // `count` (1 to 3) device tensors of n[k] elements and one dtype; factor is a device float. All
 // pointers 16-byte aligned but factor's. Enqueued on `stream`.

@@ -100,6 +100,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                                         vp, vp, vp, vp, vp, vp, ctypes.POINTER(AdamConfig), i64, ctypes.c_int,
                                         ctypes.c_int, ctypes.c_int, vp, sz, vp, ctypes.POINTER(HeadStepTiming)]
     lib.lce_head_train_step.restype = ctypes.c_int
+    lib.lce_internal_tiles.argtypes = [i64, i64, i64, ctypes.c_int, ctypes.c_int, i64, ctypes.POINTER(ctypes.c_int32)]
+    lib.lce_internal_tiles.restype = ctypes.c_int
     lib.lce_internal_scale.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(i64), ctypes.c_int,
                                        ctypes.c_int, vp, vp]
     lib.lce_internal_scale.restype = ctypes.c_int
@@ -166,6 +168,19 @@ def plan_info(N: int, H: int, V: int, dtype=torch.bfloat16, with_backward: bool 
     if st != LCE_OK:
         raise LCEError(st, "lce_plan_info")
     return info.as_dict()
+
+
+# The library's tiles (rows x columns of a workgroup; "xb": gemm_xb_kernel's 256 x 256).
+_TILES = ("xb", "256", "128", "64", "128x64")
+
+
+def _plan_tiles(N: int, H: int, V: int, dtype=torch.bfloat16, with_backward: bool = True, chunk_tokens: int = 0) -> tuple:
+    """The tiles of a call's logits, dH and dW (forward only: None for the latter two), for tests."""
+    tiles = (ctypes.c_int32 * 3)()
+    st = load_library().lce_internal_tiles(N, H, V, DTYPES[dtype], int(with_backward), chunk_tokens, tiles)
+    if st != LCE_OK:
+        raise LCEError(st, "lce_internal_tiles")
+    return tuple(_TILES[t] if t >= 0 else None for t in tiles)
 
 
 def auto_chunk_tokens(N: int, H: int, V: int, dtype=torch.bfloat16) -> int:
