@@ -652,7 +652,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
               if (inside(i, r)) mx = fmaxf(mx, acc[i][j][r]);
           mx = fmaxf(mx, __shfl_xor(mx, 32));
           m_ref = mx;
-          ml = mx * kLog2e;
+          ml = mx == -INFINITY ? 0.f : mx * kLog2e;  // a slice of -inf logits alone sums to 0
         }
         // Every token block that holds a token of the chunk is written whole: target-referenced,
         // the lanes of tokens at or beyond N store zeros (the dW GEMM sums over the last block).

@@ -87,10 +87,14 @@ def test_forward_in_every_tile(lce, N, H, V, dtype, tile):  # noqa: F811
     assert np.abs(lse.cpu().numpy() - ref["lse"]).max() <= TOL[dtype][0] * np.abs(ref["lse"]).max()
 
 
-@pytest.mark.parametrize("N,H,V,lo,hi", [(65, 72, 3001, 0, 40), (65, 72, 3001, 64, 96), (64, 64, 40000, 128, 256)])
-def test_forward_with_slices_of_minus_inf(lce, N, H, V, lo, hi):  # noqa: F811
-    """Ids whose logits are -inf add nothing to a token's sum, also where they fill a whole partial (64 x 64 and
-    128 x 64 tiles: 32 and 128 ids): the other ids' losses, of the oracle without them."""
+@pytest.mark.parametrize("N,H,V,lo,hi,tile", [
+    (65, 72, 3001, 0, 40, "64"), (65, 72, 3001, 64, 96, "64"), (64, 64, 40000, 128, 256, "128x64"),
+    (257, 264, 33001, 256, 400, "128"), (69, 288, 25521, 128, 256, "256"), (400, 4096, 20003, 128, 256, "xb"),
+    (257, 5128, 30003, 0, 256, "xb")])
+def test_forward_with_slices_of_minus_inf(lce, N, H, V, lo, hi, tile):  # noqa: F811
+    """Ids whose logits are -inf add nothing to a token's sum, also where they fill a whole partial (32 or 128
+    ids, by the tile): the other ids' losses, of the oracle without them."""
+    assert _plan_tiles(N, H, V, torch.bfloat16, False)[0] == tile
     d = workloads.make_inputs("llama3_8b", seed=33, N=N, H=H, V=V, dtype="bf16")
     hidden = d["hidden"].abs() + 0.01
     weight, labels = d["weight"].clone(), torch.arange(N) + hi
