@@ -587,22 +587,26 @@ __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, int run
     sched();
   };
 
-  // 16-bit dW accumulation: the tile's current dW values, the 16-byte row pieces that the epilogue
+  // 16-bit dW accumulation: the wave's current dW values, the 16-byte row pieces that the epilogue
   // stores, loaded while the pipeline fills, are the accumulators' starting values (divided by the
-  // factor that the epilogue applies).
+  // factor that the epilogue applies). Rows at or beyond M read zeros, columns at or beyond N whatever
+  // is there (the epilogue stores neither): a branch per piece made the compiler wait for each fp16
+  // piece before it requested the next.
   constexpr bool kPreload = EPI == EPI_DW && kEsz == 2;
   const bool accumulate = EPI == EPI_DW && g.mode == DW_ACCUMULATE;
   u32x4 prev[kPreload ? NI : 1][NJ / 2];
   if constexpr (kPreload) {
     if (accumulate) {
+      const uint32_t pitch = (uint32_t)g.ldo * 2u;
+      const __amdgpu_buffer_rsrc_t rp = make_rsrc(
+          (const void*)uniform64((uint64_t)((const T*)g.out + (size_t)mw * g.ldo)),
+          __builtin_amdgcn_readfirstlane((uint32_t)max(0, min(16 * NI, g.M - mw)) * pitch));
+      const uint32_t voff = (uint32_t)(lane & 15) * pitch + (uint32_t)(nw + 8 * (lane >> 4)) * 2u;
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; j += 2) {
-          const int row = mw + 16 * i + (lane & 15), col = nw + 16 * j + 8 * (lane >> 4);
-          prev[i][j / 2] = (row < g.M && col < g.N) ? *(const u32x4*)((const T*)g.out + (size_t)row * g.ldo + col)
-                                                    : (u32x4){};
-        }
+        for (int j = 0; j < NJ; j += 2)
+          prev[i][j / 2] = load16(rp, voff + 32u * j, __builtin_amdgcn_readfirstlane((uint32_t)(16 * i) * pitch));
     }
   }
   const int nk = (ke - kb + kBK - 1) / kBK;

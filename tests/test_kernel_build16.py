@@ -31,6 +31,19 @@ def test_main_loop(asm, t, e, a, c, tile):  # noqa: F811
     assert count(lambda x: x.startswith("ds_read_b64_tr_b16")) == (8 * ni if t != "f" and a else 0)
 
 
+@pytest.mark.parametrize("t", ["DF16b", "DF16_"])
+@pytest.mark.parametrize("tile", ["Tile256", "Tile128", "Tile64"])
+def test_dw_preload_is_in_flight_together(asm, t, tile):  # noqa: F811
+    """The earlier chunks' dW of an accumulating tile: every piece requested before any is waited for."""
+    bm, bn, wm, wn = TILES[tile]
+    name = f"_ZN3lce14gemm_xs_kernelI{t}Li3ELi2ELb0ENS_4TileILi{bm}ELi{bn}ELi{wm}ELi{wn}EEEEEvNS_8GemmArgsE"
+    code = _main_loop(asm, name, with_prologue=True)
+    code = code[:next(i for i, x in enumerate(code) if x.startswith("buffer_load") and x.endswith("lds"))]
+    loads = [i for i, x in enumerate(code) if re.match(r"(global|buffer)_load_dwordx4", x)]
+    assert len(loads) == bm // wm // 16 * (bn // wn // 16) // 2
+    assert not [x for x in code[loads[0]:loads[-1]] if x.startswith("s_waitcnt") and "vmcnt" in x]
+
+
 def _swz_k(r):
     return (r ^ (r >> 3)) & 7
 
