@@ -86,6 +86,11 @@ typedef enum { LCE_REDUCTION_NONE = 0, LCE_REDUCTION_MEAN = 1, LCE_REDUCTION_SUM
  * carried across chunks in fp32 (see lce_plan_info), and O(chunk_tokens * (V / 8 + H) + N)
  * forward only (per-slice partials instead); the logits-shaped buffer is never larger than W, or
  * than twice W where it avoids the fp32 carry (unless the caller's chunk_tokens says so, or H < 64).
+ * Where dH's contraction is split (dh_splits > 1, see lce_plan_info), its fp32 partial sums take
+ * dh_splits * chunk_tokens * H * 4 bytes more: at most the size of W or 64 MB, whichever is larger, with
+ * automatic chunks (FP32: or eight splits); with the caller's chunk_tokens at most the size of the
+ * logits-shaped buffer or eight splits, whichever is larger. The RMSNorm variants keep them, and one
+ * chunk of fp32 rows where nothing is split.
  * Returns 0 for invalid arguments.
  */
 size_t lce_workspace_size(int64_t N, int64_t H, int64_t V, int dtype, int with_backward,

@@ -252,7 +252,8 @@ bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_
 // that fills the device: the fp32 partials cost their write and read (about 6 TB/s). (The sum's launch
 // counts as 1 us: at sizes where its few us matter the alternatives are as close.)
 // A split has to win by 5% (at nearly full grids the clock makes up for idle CUs), and its
-// partials stay below the size of W (or 64 MB). Of the 256 x 256 kernels, the eight waves of Tile256
+// partials stay below the size of W (or 64 MB), with the caller's own chunk_tokens, which asks for little
+// memory where it is small, below the size of the chunk's e (or eight splits). Of the 256 x 256 kernels, the eight waves of Tile256
 // are ahead (H = 4096, V = 128256, 4096 tokens: 2.84 ms against 2.94), gemm_xb_kernel only for narrow H
 // and long K (H = 768, V = 128256, 2048 tokens: 0.342 ms against 0.358). 16-bit Tile128 is for small
 // grids, which it cuts finer in fewer splits (H = 768, V = 50257, 1024 tokens: 75 us in ten splits
@@ -275,9 +276,10 @@ int fp32_min_splits(const Plan& p, int64_t kblocks, int64_t tokens) {
   }
   return splits;
 }
-void plan_dh(Plan& p, int64_t kblocks, int64_t fp32_tokens) {
+void plan_dh(Plan& p, int64_t kblocks, int64_t fp32_tokens, bool own_chunk) {
   const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 || p.V < 100000 ? TILE_256 : TILE_XB;
-  const int64_t cap = std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
+  const int64_t cap = own_chunk ? std::max(p.ncp * p.ez_kp * 32, 8 * p.nc * p.H * 4)
+                                : std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
   const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks, fp32_tokens) : 1;
   double best = 1e300;
   for (const GemmTile t : {big, TILE_128, TILE_64}) {
@@ -308,7 +310,7 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   if (H % (16 / p.esz) != 0) return LCE_ERR_UNSUPPORTED;
   const int64_t lim = (int64_t(1) << 31) - 1;
   // Automatic chunks: a training step keeps one chunk's e/dZ, so its chunks stay small; a forward
-  // call keeps only per-slice partials (N V / 16 bytes), so it takes up to 16384 tokens at once
+  // call keeps only per-slice partials (N V / 16 bytes, of 32-row slices N V / 4), so it takes up to 16384 tokens at once
   // (one launch of the logits GEMM instead of several, each with a partly empty last wave).
   auto copies_fit = [&](int64_t tokens) {  // 32-bit limits of a chunk's two blocked copies of X
     if (tokens > lim || H > lim) return false;
@@ -358,7 +360,7 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
     const int64_t kbk = kTileBytes / p.esz;
     const int64_t kblocks = cdiv(V, kbk);
     const int64_t fp32_tokens = chunk_tokens == 0 ? half_chunk(N, H) : nc;
-    plan_dh(p, kblocks, fp32_tokens);
+    plan_dh(p, kblocks, fp32_tokens, chunk_tokens != 0);
     p.dw_run = round_up(p.esz == 4 ? cdiv(nc, cdiv(nc, fp32_tokens)) : nc, kbk);
     p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;
     p.tile_dw = dw_tile(nc, H, V, p.esz);

@@ -63,3 +63,22 @@ def test_wide_rows_are_accepted_forward_only():
     """More than 16384 tokens in chunks of half of them, where the half rounded up would not fit the limit."""
     info = lce.plan_info(40068, 26744, 56849, torch.float32, with_backward=False)
     assert info["chunk_tokens"] == 20032 and info["chunks"] == 3
+
+
+def test_dh_partials_stay_within_their_bound():
+    """dH's fp32 partials: below W (or 64 MB) with automatic chunks; below the chunk's e, or in eight splits,
+    with the caller's chunk, so that a small one keeps the workspace small."""
+    rng = random.Random(13)
+    cases = [(203, 5472, 135757, "fp32", 0), (8192, 4096, 128256, "bf16", 64), (4096, 768, 50257, "bf16", 64)]
+    for _ in range(2000):
+        N, H, V = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((64, 16384), (32, 1536), (64, 152064)))
+        cases.append((N, 8 * H, V, rng.choice(("bf16", "fp16", "fp32")), rng.choice((0, 64, 64 * rng.randint(1, 64)))))
+    for N, H, V, dtype, chunk in cases:
+        size = 4 if dtype == "fp32" else 2
+        info = lce.plan_info(N, H, V, {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype], True, chunk)
+        if info["dh_splits"] == 1:
+            continue
+        tokens = info["chunk_tokens"]
+        part, eight = info["dh_splits"] * tokens * H * 4, 8 * tokens * H * 4
+        e = -(-tokens // 64) * 64 * -(-V // 256) * 256 * size
+        assert part <= (max(e, eight) if chunk else max(64 << 20, V * H * size, eight if dtype == "fp32" else 0)), (N, H, V, dtype, chunk)
