@@ -277,12 +277,13 @@ int fp32_min_splits(const Plan& p, int64_t kblocks, int64_t tokens) {
   return splits;
 }
 void plan_dh(Plan& p, int64_t kblocks, int64_t fp32_tokens, bool own_chunk) {
-  const GemmTile big = p.esz == 4 ? TILE_128 : p.H > 1024 || p.V < 100000 ? TILE_256 : TILE_XB;
+  const GemmTile big = p.H > 1024 || p.V < 100000 ? TILE_256 : TILE_XB;  // 16-bit only
   const int64_t cap = own_chunk ? std::max(p.ncp * p.ez_kp * 32, 8 * p.nc * p.H * 4)
                                 : std::max<int64_t>(int64_t(64) << 20, p.V * p.H * p.esz);
   const int64_t least = p.esz == 4 ? fp32_min_splits(p, kblocks, fp32_tokens) : 1;
   double best = 1e300;
   for (const GemmTile t : {big, TILE_128, TILE_64}) {
+    if (t == big && p.esz == 4) continue;
     if (t == TILE_128 && p.esz == 2 && p.nc >= 1024 && (p.H > 1024 || p.nc > 2048)) continue;
     const int64_t tiles = tile_count(t, p.H, p.nc);
     for (int64_t s = least; s <= std::min<int64_t>(kblocks, 128); ++s) {
@@ -453,11 +454,15 @@ hipError_t launch_gemm(GemmTile tile, const GemmArgs& g, hipStream_t s) {
     return launch_tiles(gemm_xs_kernel<T, EPI, AL, KCHECK, C>, configured[k], C::kBM, C::kBN, C::kThreads, C::kSmem, g, s);
   };
   if (tile == TILE_64) return xs(Tile64{}, 0);
-  if constexpr (EPI == EPI_LSE_FWD || EPI == EPI_LSE_BWD)
-    if (tile == TILE_128x64) return xs(Tile128x64{}, 4);
   if (tile == TILE_128) return xs(Tile128{}, 1);
-  if (tile == TILE_256) return xs(Tile256{}, 2);
-  return launch_tiles(gemm_xb_kernel<T, EPI, AL, KCHECK>, configured[3], kTile, kTile, kGemmThreads, kXbSmem, g, s);
+  if constexpr (sizeof(T) == 2) {  // the plans' rules give fp32 none of these
+    if constexpr (EPI == EPI_LSE_FWD || EPI == EPI_LSE_BWD)
+      if (tile == TILE_128x64) return xs(Tile128x64{}, 4);
+    if (tile == TILE_256) return xs(Tile256{}, 2);
+    if (tile == TILE_XB)
+      return launch_tiles(gemm_xb_kernel<T, EPI, AL, KCHECK>, configured[3], kTile, kTile, kGemmThreads, kXbSmem, g, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 // Optional events for a caller that streams dW out as it is produced: the last chunk's dW GEMM runs

@@ -12,17 +12,17 @@
 // transposed or copied and only the small X chunk is rearranged (twice per chunk).
 //
 // One workgroup computes a 256 x 256 tile of C with four waves (2 x 2), each wave a 128 x 128
-// sub-tile held as 4 x 4 blocks of the 32x32 MFMA accumulator (256 fp32 per lane). K advances in
-// K-tiles of 64 bf16 (32 fp32); A's K-tile is 32 KB of LDS either way: 256 rows of 128 bytes
-// (K-contig) or 64 (32) K-rows of 512 (1024) bytes (MN-contig and blocked). Global loads are 16
+// sub-tile held as 4 x 4 blocks of the 32x32 MFMA accumulator (256 fp32 per lane). The operands are
+// 16-bit (fp32's contractions are all gemm_xs_kernel's, lce_gemm16.hpp). K advances in
+// K-tiles of 64; A's K-tile is 32 KB of LDS in either layout: 256 rows of 128 bytes
+// (K-contig) or 64 K-rows of 512 bytes (MN-contig and blocked). Global loads are 16
 // bytes per lane. Buffer descriptors turn rows beyond M (K-contig) or K-rows beyond the K range
 // (MN-contig and blocked, one descriptor per K-tile), and K-tiles past the end, into zeros.
 //
 // A's fragments: for the 32x32x16 bf16 MFMA a lane supplies 8 consecutive K of one row. K-contig
 // tiles give them with one ds_read_b128; MN-contig bf16 tiles with two ds_read_b64_tr_b16 (each
 // 16-lane group reads four K-rows of 16 columns and the LDS transposes them so that lane j
-// receives column j of the four rows); MN-contig fp32 tiles with four ds_read_b32. The 16-byte
-// slots of every LDS row are XOR-swizzled so that these reads are free of bank conflicts. A
+// receives column j of the four rows). The 16-byte slots of every LDS row are XOR-swizzled so that these reads are free of bank conflicts. A
 // blocked A is fetched into the very LDS slots an MN-contig one would occupy. Fragments are
 // double-buffered in registers: the reads for the next 32 bytes of K are in flight while the
 // MFMAs of the current ones run.
@@ -57,7 +57,6 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 constexpr int kTile = 256;                       // BM = BN
 constexpr int kTileBytes = 128;                  // bytes of K per row of a K-contig K-tile
@@ -120,10 +119,6 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, char* lds, uint3
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)lds, 16, voff, soff, 0, 0);
 }
 
-__device__ __forceinline__ i16x4 read_tr(const char* lds) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)lds);
-}
-
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -161,15 +156,6 @@ __device__ __forceinline__ void mfma_pair<bf16>(f32x16& c, const f32x4& a, const
 template <>
 __device__ __forceinline__ void mfma_pair<f16>(f32x16& c, const f32x4& a, const f32x4& b) {
   c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-template <>
-__device__ __forceinline__ void mfma_pair<float>(f32x16& c, const f32x4& a, const f32x4& b) {
-  // 8 fp32 of K: each 32x32x2 step takes element s of both lanes' 4-vectors.
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0], b[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1], b[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[2], b[2], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[3], b[3], c, 0, 0, 0);
 }
 
 __device__ __forceinline__ void store4(bf16* p, float a, float b, float c, float d) {
@@ -289,11 +275,10 @@ __device__ __forceinline__ void store_frag32(char* p, const f32x16& v) {
 // (k % 32 + 32 ((m s / 16) % 2)) 16 + (m s) % 16, s = sizeof(T): a 16-byte piece holds 16 / s
 // consecutive ids of one token. 16-bit: each load fetches one whole fragment (1 KB, 32 tokens by
 // 16 ids) into LDS as it is, up to a permutation of its pieces, and the transposing fragment reads
-// find each lane's four ids of a token inside a piece. fp32: each load fetches the MN-contig
-// pieces (4 ids of one token at 512 c + 16 (k % 32) past the token block's start of the tile's
-// ids, c the MN slot), 32 scattered pieces per load, into the MN-contig LDS layout.
+// find each lane's four ids of a token inside a piece. (fp32's: Operand16 in lce_gemm16.hpp.)
 template <typename T, int AL>
 struct Operand {
+  static_assert(sizeof(T) == 2);
   static constexpr int kEsz = (int)sizeof(T);
   static constexpr int kBK = kTileBytes / kEsz;       // K per K-tile
   static constexpr int kMnRowBytes = kTile * kEsz;    // MN-contig: bytes per K-row
@@ -331,54 +316,38 @@ struct Operand {
       for (int i = 0; i < 4; ++i) frag[i] = (wsub + 32 * i + (lane & 31)) * kTileBytes;
     } else {
       base = BLK ? (const char*)p + (size_t)mn0 * 32 * kEsz : (const char*)p + (size_t)mn0 * kEsz;
-      if constexpr (kEsz == 2) {
-        const int g = lane >> 4, ip = lane & 15;
-        if constexpr (BLK) {
-          // The LDS K-tile holds the 32 fragments of the K-tile's two token blocks b by the
-          // tile's 16 id fragments c, fragment (b, c) in 1 KB slot 16 b + c. Piece P of a fragment
-          // (token P%32, id half P/32) sits at 16 Q, Q = P ^ 4 (P/32) ^ 8 (c%2), so that the
-          // fragment reads below are free of bank conflicts. Load j of wave w fills slot 8w + j:
-          // token block w/2, c = 8 (w%2) + j; lane l fetches piece l ^ 4 (l/32) ^ 8 (j%2).
-          row_off = (uint32_t)(w >> 1) * (uint32_t)ld * 1024u + (uint32_t)(w & 1) * 8192u;
-          row_step = 1024u;
-          slot_x = (uint32_t)((lane ^ (4 * (lane >> 5))) << 4);
-          // Transposed reads: 16-lane group g, lane i' = l%16 reads token 16p + 8(g/2) + 4s + i'/4
-          // of the K-tile, ids wsub + 32i + 16(g%2) + 4(i'%4) .. + 3: slot 16 (p/2) + (wsub +
-          // 32i)/16 + g%2, Q = i'/4 + 4 (s ^ h) + 8 ((g/2) ^ (g%2)) + 16 (p%2) + 32 h with
-          // h = (i'%4)/2, byte 8 (i'%2) of the piece. frag[0] is the address at p = s = i = 0;
-          // s flips bit 6, p and i add 16384 (p/2) + 256 (p%2) + 2048 i.
-          const int h = (ip & 3) >> 1;
-          frag[0] = (wsub / 16 + (g & 1)) * 1024 + 16 * ((ip >> 2) + 4 * h + 8 * ((g >> 1) ^ (g & 1)) + 32 * h) +
-                    8 * (ip & 1);
-        } else {
-          // Load j of wave w: lane l holds K-row kr = 16w + 2j + l/32, slot l%32, which is logical
-          // slot (l%32) ^ swz_mn(kr), and swz_mn(kr) = 4 (l/32) ^ 10 (j&1) ^ 16 ((j>>2)&1).
-          row_off = (uint32_t)(16 * w + (lane >> 5)) * (uint32_t)ld * 2;
-          row_step = 2u * (uint32_t)ld * 2;
-          slot_x = (uint32_t)(((lane & 31) ^ (4 * (lane >> 5))) << 4);
-          // Transposed reads: 16-lane group g, lane i' = l%16 reads K-row 16p + 8(g/2) + 4s + i'/4
-          // at column wsub + 32i + 16(g%2) + 4(i'%4). The swizzle depends only on row bits 0, 1
-          // and 3, all fixed by the lane, so the address is this base plus (16p + 4s) * 512.
-          // Block i only flips address bits 6-7: its 16-byte slot is block 0's XOR 4i (the column's
-          // slot bits 2-3 come from 32i alone), so frag[i] = frag[0] ^ (i << 6).
-          const int r0 = 8 * (g >> 1) + (ip >> 2);
-          const int col = wsub + 16 * (g & 1) + 4 * (ip & 3);
-          frag[0] = r0 * kMnRowBytes + (((col >> 3) ^ swz_mn(r0)) << 4) + 8 * ((col >> 2) & 1);
-        }
+      const int g = lane >> 4, ip = lane & 15;
+      if constexpr (BLK) {
+        // The LDS K-tile holds the 32 fragments of the K-tile's two token blocks b by the
+        // tile's 16 id fragments c, fragment (b, c) in 1 KB slot 16 b + c. Piece P of a fragment
+        // (token P%32, id half P/32) sits at 16 Q, Q = P ^ 4 (P/32) ^ 8 (c%2), so that the
+        // fragment reads below are free of bank conflicts. Load j of wave w fills slot 8w + j:
+        // token block w/2, c = 8 (w%2) + j; lane l fetches piece l ^ 4 (l/32) ^ 8 (j%2).
+        row_off = (uint32_t)(w >> 1) * (uint32_t)ld * 1024u + (uint32_t)(w & 1) * 8192u;
+        row_step = 1024u;
+        slot_x = (uint32_t)((lane ^ (4 * (lane >> 5))) << 4);
+        // Transposed reads: 16-lane group g, lane i' = l%16 reads token 16p + 8(g/2) + 4s + i'/4
+        // of the K-tile, ids wsub + 32i + 16(g%2) + 4(i'%4) .. + 3: slot 16 (p/2) + (wsub +
+        // 32i)/16 + g%2, Q = i'/4 + 4 (s ^ h) + 8 ((g/2) ^ (g%2)) + 16 (p%2) + 32 h with
+        // h = (i'%4)/2, byte 8 (i'%2) of the piece. frag[0] is the address at p = s = i = 0;
+        // s flips bit 6, p and i add 16384 (p/2) + 256 (p%2) + 2048 i.
+        const int h = (ip & 3) >> 1;
+        frag[0] = (wsub / 16 + (g & 1)) * 1024 + 16 * ((ip >> 2) + 4 * h + 8 * ((g >> 1) ^ (g & 1)) + 32 * h) +
+                  8 * (ip & 1);
       } else {
-        // fp32: load j of wave w: lane l holds K-row 8w + j, slot l; fragment reads are plain.
-        // Blocked: K-row 8w + j is token 8w + j of the K-tile's one token block; slot l at 512 l.
-        if constexpr (BLK) {
-          row_off = (uint32_t)(8 * w) * 16u;
-          row_step = 16u;
-          slot_x = (uint32_t)lane << 9;
-        } else {
-          row_off = (uint32_t)(8 * w) * (uint32_t)ld * 4;
-          row_step = (uint32_t)ld * 4;
-          slot_x = (uint32_t)(lane * 16);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) frag[i] = (4 * (lane >> 5)) * kMnRowBytes + (wsub + 32 * i + (lane & 31)) * 4;
+        // Load j of wave w: lane l holds K-row kr = 16w + 2j + l/32, slot l%32, which is logical
+        // slot (l%32) ^ swz_mn(kr), and swz_mn(kr) = 4 (l/32) ^ 10 (j&1) ^ 16 ((j>>2)&1).
+        row_off = (uint32_t)(16 * w + (lane >> 5)) * (uint32_t)ld * 2;
+        row_step = 2u * (uint32_t)ld * 2;
+        slot_x = (uint32_t)(((lane & 31) ^ (4 * (lane >> 5))) << 4);
+        // Transposed reads: 16-lane group g, lane i' = l%16 reads K-row 16p + 8(g/2) + 4s + i'/4
+        // at column wsub + 32i + 16(g%2) + 4(i'%4). The swizzle depends only on row bits 0, 1
+        // and 3, all fixed by the lane, so the address is this base plus (16p + 4s) * 512.
+        // Block i only flips address bits 6-7: its 16-byte slot is block 0's XOR 4i (the column's
+        // slot bits 2-3 come from 32i alone), so frag[i] = frag[0] ^ (i << 6).
+        const int r0 = 8 * (g >> 1) + (ip >> 2);
+        const int col = wsub + 16 * (g & 1) + 4 * (ip & 3);
+        frag[0] = r0 * kMnRowBytes + (((col >> 3) ^ swz_mn(r0)) << 4) + 8 * ((col >> 2) & 1);
       }
     }
   }
@@ -386,9 +355,8 @@ struct Operand {
   // The compile-time XOR part of load j's offset.
   static __device__ __forceinline__ constexpr uint32_t xor_j(int j) {
     if constexpr (!MN) return (uint32_t)(j << 4);
-    else if constexpr (kEsz == 2 && BLK) return (uint32_t)((j & 1) ? 128 : 0);
-    else if constexpr (kEsz == 2) return (uint32_t)((((j & 1) ? 10 : 0) ^ (((j >> 2) & 1) ? 16 : 0)) << 4);
-    else return 0u;
+    else if constexpr (BLK) return (uint32_t)((j & 1) ? 128 : 0);
+    else return (uint32_t)((((j & 1) ? 10 : 0) ^ (((j >> 2) & 1) ? 16 : 0)) << 4);
   }
 
   // Descriptor for K-tile t. MN-contig: its valid K-rows only, so that rows at or beyond ke,
@@ -452,12 +420,12 @@ struct Operand {
     }
   }
 
-  // 16-bit MN-contig and blocked A: the fragment reads address LDS through per-lane registers that
+  // MN-contig and blocked A: the fragment reads address LDS through per-lane registers that
   // hold the whole address in the current pair of ring slots (slots 0-1 or 2-3), so that the slot
   // within the pair, the K-pair and the block enter as the read's immediate offset and no address
   // arithmetic sits between the MFMAs. MN: xa[i] for block i (frag[0] ^ (i << 6)); blocked: xa[0]
   // and xa[1] for the two reads of a fragment (frag[0], frag[0] ^ 64). All plus the ring's base.
-  static constexpr int kXa = (kEsz == 2 && MN) ? (BLK ? 2 : 4) : 0;
+  static constexpr int kXa = MN ? (BLK ? 2 : 4) : 0;
   uint32_t xa[kXa > 0 ? kXa : 1];
   __device__ __forceinline__ void init_xa(uint32_t ring_base) {
     if constexpr (kXa > 0) {
@@ -492,51 +460,14 @@ struct Operand {
     return __builtin_bit_cast(f32x4, v);
   }
 
-  // Fragment of K-pair p of block i from the LDS tile at `st`.
+  // K-contig: the fragment of K-pair p of block i from the LDS tile at `st`.
   __device__ __forceinline__ f32x4 fragment(const char* st, int p, int i, int khalf, int sw) const {
-    if constexpr (!MN) {
-      return *(const f32x4*)(st + frag[i] + (((2 * p + khalf) ^ sw) << 4));
-    } else if constexpr (kEsz == 2 && BLK) {
-      // As below; the two reads of a fragment differ in address bit 6 (s), which the tile base
-      // (a multiple of 1 KB) leaves alone, and p and i only add an immediate offset.
-      i16x4 lo, hi;
-      uint32_t a, b;
-      asm volatile(
-          "v_add_u32 %2, %4, %5\n\t"
-          "v_xor_b32 %3, 64, %2\n\t"
-          "ds_read_b64_tr_b16 %0, %2 offset:%6\n\t"
-          "ds_read_b64_tr_b16 %1, %3 offset:%6"
-          : "=v"(lo), "=v"(hi), "=&v"(a), "=&v"(b)
-          : "s"((uint32_t)(uintptr_t)(lds_void*)st), "v"(frag[0]), "i"(16384 * (p >> 1) + 256 * (p & 1) + 2048 * i));
-      const i16x4 v[2] = {lo, hi};
-      return __builtin_bit_cast(f32x4, v);
-    } else if constexpr (kEsz == 2) {
-      // Issued as inline assembly: the compiler cannot tell which LDS bytes the transposing read
-      // builtin touches, and so would wait for every outstanding LDS-DMA load before it. The
-      // caller waits for these reads itself (see sync_frags). The address, (frag[0] ^ (i << 6)) +
-      // tile base, is formed here too: hoisted, the per-block addresses of two such operands would
-      // be spilled.
-      i16x4 lo, hi;
-      uint32_t a;
-      asm volatile(
-          "v_xor_b32 %2, %3, %4\n\t"
-          "v_add_u32 %2, %5, %2\n\t"
-          "ds_read_b64_tr_b16 %0, %2 offset:%6\n\t"
-          "ds_read_b64_tr_b16 %1, %2 offset:%7"
-          : "=v"(lo), "=v"(hi), "=&v"(a)
-          : "s"(i << 6), "v"(frag[0]), "s"((uint32_t)(uintptr_t)(lds_void*)st), "i"((16 * p) * kMnRowBytes),
-            "i"((16 * p + 4) * kMnRowBytes));
-      const i16x4 v[2] = {lo, hi};
-      return __builtin_bit_cast(f32x4, v);
-    } else {
-      const char* q = st + frag[i] + (8 * p) * kMnRowBytes;
-      return (f32x4){*(const float*)q, *(const float*)(q + kMnRowBytes), *(const float*)(q + 2 * kMnRowBytes),
-                     *(const float*)(q + 3 * kMnRowBytes)};
-    }
+    static_assert(!MN);
+    return *(const f32x4*)(st + frag[i] + (((2 * p + khalf) ^ sw) << 4));
   }
 };
 
-// 16-bit dW accumulation (chunks after the first): the wave's current dW values, loaded raw while
+// dW accumulation (chunks after the first): the wave's current dW values, loaded raw while
 // the pipeline fills, then the accumulators' starting values. Each lane loads the two 16-byte row
 // pieces that store_row32 writes from it (lanes l and l + 32 cover 32 contiguous bytes of a row per
 // load), and one v_permlane32_swap per dword -- the inverse of regroup32's, which is its own
@@ -609,11 +540,10 @@ __device__ __forceinline__ float dw_prev_scale(const GemmArgs& g) {
 // operand swap (LSE, STORE), accumulator element r of block (i, j) sits at row = 32i + 8(r/4) +
 // 4(l/32) + r%4, col = 32j + l%32 of the sub-tile; with it (DW), at row = 32i + l%32,
 // col = 32j + 8(r/4) + 4(l/32) + r%4.
-// PRELOADED (DW): the accumulators started from the tile's current dW values.
-template <typename T, int EPI, bool PRELOADED>
+// DW: the accumulators started from the tile's current dW values (or zero).
+template <typename T, int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4][4], int mw, int nw, int split,
-                                              bool accumulate, int n0, const char* refs_lds) {
-  constexpr int kEsz = (int)sizeof(T);
+                                              int n0, const char* refs_lds) {
   const int lane = lane_id();
   const int sub4 = 4 * (lane >> 5);
   const int l32 = lane & 31;
@@ -671,22 +601,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
           }
           if constexpr (EPI == EPI_LSE_BWD) {
             if (store) {
-              if constexpr (kEsz == 2) {
-                // Whole 128-row wave slices: the blocked rows cover M rounded up to 256, and rows
-                // at or beyond M hold exp = 0 here.
-                store_frag32<T>(e_blk + (size_t)((mw + 32 * i) >> 4) * 1024, ev);
-              } else {
-                // fp32: a K-pair is 8 ids, half of it per lane half. The dH GEMMs read every K-quad
-                // (16 ids) that holds an id below M whole, so such a K-quad is stored whole: its ids
-                // at or beyond M hold exp = 0 here, and nothing stale from the workspace reaches it.
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                  const int kp_row = mw + 32 * i + 8 * q;
-                  if (FULL || (kp_row & ~15) < g.M)
-                    store4((T*)(e_blk + (size_t)(kp_row >> 3) * 1024), ev[4 * q], ev[4 * q + 1], ev[4 * q + 2],
-                           ev[4 * q + 3]);
-                }
-              }
+              // Whole 128-row wave slices: the blocked rows cover M rounded up to 256, and rows
+              // at or beyond M hold exp = 0 here.
+              store_frag32<T>(e_blk + (size_t)((mw + 32 * i) >> 4) * 1024, ev);
             }
           }
         }
@@ -702,7 +619,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
   } else if constexpr (EPI == EPI_STORE) {
     // C^T token-major: column n = nw + 32j + l%32 of C is row n of the output, and the lane's four
     // consecutive rows of C per (i, q) are four consecutive elements of it. M (the output's row
-    // length) is a multiple of 8 for 16-bit types and of 4 for fp32, so pieces are all in or out.
+    // length) is a multiple of 8, so pieces are all in or out.
     // mode 1: fp32 partials, split s at out + s * N * ldo.
     const float sc = dz_epilogue_scale<T>(g.n_valid, g.mean);
 #pragma unroll
@@ -726,28 +643,17 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
           }
       } else {
         T* o = (T*)g.out + (size_t)col * g.ldo;
-        if constexpr (kEsz == 2) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if constexpr (Storage<T>::kDzUnscaled) acc[i][j] *= sc;
-            const int r0 = mw + 32 * i + 8 * (lane >> 5);
-            store_row32(o + mw + 32 * i, acc[i][j], r0 < g.M, r0 + 16 < g.M);
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int row = mw + 32 * i + 8 * q + sub4;
-              if (row < g.M)
-                store4(o + row, acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-            }
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (Storage<T>::kDzUnscaled) acc[i][j] *= sc;
+          const int r0 = mw + 32 * i + 8 * (lane >> 5);
+          store_row32(o + mw + 32 * i, acc[i][j], r0 < g.M, r0 + 16 < g.M);
         }
       }
     }
   } else {
     // DW, swapped layout: lane owns rows mw + 32i + l%32 and 4 consecutive columns per (j, q).
-    // N (the output pitch) is a multiple of 4 here, so a 4-column group is all in or all out.
+    // N (the output pitch) is a multiple of 8, so a 4-column group is all in or all out.
     const float sc = dz_epilogue_scale<T>(g.n_valid, g.mean);
     if (g.mode >= DW_ACC32_FIRST) {
       // fp32 cross-chunk accumulator: acc32 (+)= sc * C, or at the last chunk dW = acc32 + sc * C
@@ -784,32 +690,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[4
     for (int i = 0; i < 4; ++i) {
       const int row = mw + 32 * i + l32;
       if (row >= g.M) continue;
-      if constexpr (PRELOADED) {  // EPI_DW, 16-bit: the accumulators already hold the earlier chunks' sum
-        T* o = (T*)g.out + (size_t)row * g.ldo;
+      // The accumulators already hold the earlier chunks' sum.
+      T* o = (T*)g.out + (size_t)row * g.ldo;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if constexpr (Storage<T>::kDzUnscaled) acc[i][j] *= sc;
-          const int c0 = nw + 32 * j + 8 * (lane >> 5);
-          store_row32(o + nw + 32 * j, acc[i][j], c0 < g.N, c0 + 16 < g.N);
-        }
-      } else {  // EPI_DW, fp32: add the earlier chunks' sum here
-        T* o = (T*)g.out + (size_t)row * g.ldo;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          f32x4 base[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int col = nw + 32 * j + 8 * q + sub4;
-            base[q] = (!PRELOADED && accumulate && col < g.N) ? load4(o + col) : (f32x4){};
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int col = nw + 32 * j + 8 * q + sub4;
-            if (col < g.N)
-              store4(o + col, base[q][0] + sc * acc[i][j][4 * q], base[q][1] + sc * acc[i][j][4 * q + 1],
-                     base[q][2] + sc * acc[i][j][4 * q + 2], base[q][3] + sc * acc[i][j][4 * q + 3]);
-          }
-        }
+      for (int j = 0; j < 4; ++j) {
+        if constexpr (Storage<T>::kDzUnscaled) acc[i][j] *= sc;
+        const int c0 = nw + 32 * j + 8 * (lane >> 5);
+        store_row32(o + nw + 32 * j, acc[i][j], c0 < g.N, c0 + 16 < g.N);
       }
     }
   }
@@ -981,10 +868,12 @@ __device__ __forceinline__ void gemm_xb_tile(const GemmArgs& g, int bid, char* s
   f32x4 fa[2][4];
   auto read_frags = [&](int t, int p, int buf) {
     const char* sa = smem + (t & (kXbASlots - 1)) * kOperandBytes;
+    if constexpr (!kAmn) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fa[buf][i] = opa.fragment(sa, p, i, khalf, swi[i]);
+      for (int i = 0; i < 4; ++i) fa[buf][i] = opa.fragment(sa, p, i, khalf, swi[i]);
+    }
   };
-  // 16-bit MN-contig / blocked A: reads through the address registers. NEXT: the pair of slots after
+  // MN-contig / blocked A: reads through the address registers. NEXT: the pair of slots after
   // the current one (the addresses moved by pair_delta for these reads only).
   constexpr bool kXread = Operand<T, AL>::kXa > 0;
   int pair_delta = 2 * kOperandBytes;  // current pair 0-1: the next is 2 slots up, then down
@@ -1006,7 +895,7 @@ __device__ __forceinline__ void gemm_xb_tile(const GemmArgs& g, int bid, char* s
   // the start of each section wait for all earlier LDS traffic (the previous section's reads, long
   // since done), with the fragment registers as operands so that no MFMA moves above the wait.
   auto sync_frags = [&]() {
-    if constexpr (kAmn && kEsz == 2) {
+    if constexpr (kAmn) {
       asm volatile("s_waitcnt lgkmcnt(0)"
                    : "+v"(fa[0][0]), "+v"(fa[0][1]), "+v"(fa[0][2]), "+v"(fa[0][3]), "+v"(fa[1][0]),
                      "+v"(fa[1][1]), "+v"(fa[1][2]), "+v"(fa[1][3])
@@ -1026,7 +915,6 @@ __device__ __forceinline__ void gemm_xb_tile(const GemmArgs& g, int bid, char* s
   constexpr int kReads = kAmn ? 0 : 4;  // compiler-visible LDS reads per section
   // The section's LDS reads after its first MFMAs, its six loads after MFMAs 1, 3, .., 11.
   auto sched = []() {
-    if constexpr (kEsz != 2) return;  // fp32: 64 MFMAs per section; left to the compiler
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -1077,12 +965,11 @@ __device__ __forceinline__ void gemm_xb_tile(const GemmArgs& g, int bid, char* s
     sched();
   };
 
-  // 16-bit dW accumulation (chunks after the first): the tile's current dW values are loaded here,
+  // dW accumulation (chunks after the first): the tile's current dW values are loaded here,
   // raw, in flight together with the loads that fill the pipeline, and become the accumulators'
-  // starting values, so the epilogue only stores. (fp32 adds them in the epilogue instead: its
-  // 256 values per lane would not fit next to the pipeline's registers.)
+  // starting values, so the epilogue only stores.
   const int mw = m0 + wm * 128, nw = n0 + wn * 128;
-  constexpr bool kPreload = EPI == EPI_DW && kEsz == 2;
+  constexpr bool kPreload = EPI == EPI_DW;
   const bool accumulate = EPI == EPI_DW && g.mode == DW_ACCUMULATE;
   u32x4 prev[kPreload ? 4 : 1][4][2];
   if constexpr (kPreload) {
@@ -1146,7 +1033,7 @@ __device__ __forceinline__ void gemm_xb_tile(const GemmArgs& g, int bid, char* s
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   }
 
-  gemm_epilogue<T, EPI, kPreload>(g, acc, mw, nw, split, accumulate, n0, smem + kXbRefs);
+  gemm_epilogue<T, EPI>(g, acc, mw, nw, split, n0, smem + kXbRefs);
 }
 
 // One 256 x 256 tile per workgroup. With g.run_if set, the whole grid does nothing unless

@@ -16,8 +16,8 @@ import pytest
 
 from paper_2603_16428_amd import build as B
 
-# Element types: bf16 (DF16b), fp16 (DF16_), fp32 (f).
-TYPES = ("DF16b", "DF16_", "f")
+# Element types: bf16 (DF16b), fp16 (DF16_). (fp32 runs gemm_xs_kernel alone: test_kernel_build16.py.)
+TYPES = ("DF16b", "DF16_")
 # gemm_xb_kernel (B blocked, straight to registers): (epilogue, A layout 0 K-contiguous / 1 MN-
 # contiguous / 2 blocked, per-chunk K check) of the logits GEMMs (forward / backward, with and
 # without the K check), dH and dW.
@@ -71,14 +71,14 @@ def test_gemm_main_loop_has_no_scratch_traffic(asm, name):
     vload = [l for l in loop if l.startswith("buffer_load") and not l.endswith("lds")]
     writes = [l for l in loop if l.startswith("ds_write")]
     tr = [l for l in loop if l.startswith("ds_read_b64_tr_b16")]
-    # Two K-tiles per loop trip: 2 x 64 MFMA steps (x4 for fp32's 32x32x2); A by LDS-DMA (2 x 8), B
-    # fragments straight to registers (2 x 16), nothing written to LDS.
-    assert len(mfma) == (128 if "DF16" in name else 512), len(mfma)
+    # Two K-tiles per loop trip: 2 x 64 MFMA steps; A by LDS-DMA (2 x 8), B fragments straight to
+    # registers (2 x 16), nothing written to LDS.
+    assert len(mfma) == 128, len(mfma)
     assert len(dma) == 16 and len(vload) == 32 and len(writes) == 0, (len(dma), len(vload), len(writes))
-    # A in the MN-contiguous LDS layout (MN-contiguous or blocked), 16-bit: 2 transposing reads per
+    # A in the MN-contiguous LDS layout (MN-contiguous or blocked): 2 transposing reads per
     # fragment x 4 fragments per K-pair x 4 K-pairs per K-tile x 2 K-tiles.
     layout = int(name.split("ELi")[1][0])
-    assert len(tr) == (2 * 4 * 4 * 2 if "DF16" in name and layout > 0 else 0), len(tr)
+    assert len(tr) == (2 * 4 * 4 * 2 if layout > 0 else 0), len(tr)
 
 
 # ---- LDS layout model: the index formulas of the GEMM loaders and fragment reads -------------
@@ -258,20 +258,6 @@ def _blocked_decode(off, KP, esz):
     return 32 * jb + (lf & 31), (32 * q + 16 * (lf >> 5)) // esz
 
 
-@pytest.mark.parametrize("KP", [32, 16032])
-def test_blocked_a_fp32_loader_fetches_the_mn_loaders_pieces(KP):
-    # fp32 blocked A: relative to the K-tile's first token and the tile's first id, load j of wave
-    # w, lane l must fetch the piece (K-row, ids) that the MN-contiguous loader puts in the same
-    # LDS slot, inside the descriptor's range (the tile's ids in the K-tile's one token block).
-    esz = 4
-    for w in range(4):
-        for j in range(8):
-            for lane in range(64):
-                off = 8 * w * 16 + j * 16 + (lane << 9)
-                assert _blocked_decode(off, KP, esz) == (8 * w + j, 4 * lane)
-                assert off + 16 <= 256 * esz * 32
-
-
 @pytest.mark.parametrize("KP", [16, 8016])
 def test_blocked_a_16bit_loads_whole_fragments(KP):
     # 16-bit blocked A: each load reads one whole fragment (1 KB, contiguous), slot 8w + j holds
@@ -289,11 +275,10 @@ def test_blocked_a_16bit_loads_whole_fragments(KP):
             assert all((o + 16 <= tile_bytes) == (w < 2) for o in offs)
 
 
-@pytest.mark.parametrize("esz", [2, 4])
-def test_lse_epilogue_stores_e_blocked(esz):
+def test_lse_epilogue_stores_e_blocked():
     # The LSE_BWD epilogue: for block (i, j) of the wave at (mw, nw), lane l's token is column
     # nw + 32 j + l%32 and its piece of each fragment of that token block is at l * 16.
-    KP = 64 if esz == 2 else 128
+    KP, esz = 64, 2
     for mw, nw in ((0, 0), (128, 128), (768, 224)):
         for j in range(4):
             for i in range(4):
@@ -301,15 +286,10 @@ def test_lse_epilogue_stores_e_blocked(esz):
                     h = lane >> 5
                     tok = nw + 32 * j + (lane & 31)
                     e_blk = ((nw + 32 * j) >> 5) * KP * 1024 + lane * 16
-                    if esz == 2:
-                        # after regroup32: ids 8h .. and 16 + 8h .. of the 32-id segment
-                        lo = e_blk + ((mw + 32 * i) >> 4) * 1024
-                        assert _blocked_decode(lo, KP, esz) == (tok, mw + 32 * i + 8 * h)
-                        assert _blocked_decode(lo + 1024, KP, esz) == (tok, mw + 32 * i + 16 + 8 * h)
-                    else:
-                        for q in range(4):
-                            off = e_blk + ((mw + 32 * i + 8 * q) >> 3) * 1024
-                            assert _blocked_decode(off, KP, esz) == (tok, mw + 32 * i + 8 * q + 4 * h)
+                    # after regroup32: ids 8h .. and 16 + 8h .. of the 32-id segment
+                    lo = e_blk + ((mw + 32 * i) >> 4) * 1024
+                    assert _blocked_decode(lo, KP, esz) == (tok, mw + 32 * i + 8 * h)
+                    assert _blocked_decode(lo + 1024, KP, esz) == (tok, mw + 32 * i + 16 + 8 * h)
 
 
 @pytest.mark.parametrize("esz", [2, 4])

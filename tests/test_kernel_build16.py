@@ -4,15 +4,22 @@ import re
 
 import pytest
 
-from test_kernel_build import _blocked_from_k, _main_loop, asm  # noqa: F401
+from test_kernel_build import _blocked_decode, _blocked_from_k, _main_loop, asm  # noqa: F401
 
 TYPES = ("DF16b", "DF16_", "f")
 VARIANTS = [(0, 0, 0), (0, 0, 1), (1, 0, 0), (1, 0, 1), (2, 1, 0), (3, 2, 0)]  # epilogue, A layout, K check
 # BM, BN, waves along M and N.
 TILES = {"Tile256": (256, 256, 2, 4), "Tile128": (128, 256, 1, 4), "Tile64": (64, 64, 2, 2),
          "Tile128x64": (128, 64, 1, 2)}
+# fp32 runs 64 x 64 and 128 x 256 alone; 128 x 64 is for logits.
 KERNELS = [(t, e, a, c, tile) for t in TYPES for e, a, c in VARIANTS for tile in TILES
-           if tile != "Tile128x64" or e < 2]
+           if (t != "f" or tile in ("Tile64", "Tile128")) and (tile != "Tile128x64" or e < 2)]
+
+
+def test_only_reachable_tiles_are_built(asm):  # noqa: F811
+    assert not re.search(r"^_ZN3lce14gemm_xb_kernelIf", asm, re.M)
+    built = set(re.findall(r"^_ZN3lce14gemm_xs_kernelIfLi\d+ELi\d+ELb\dENS_4TileILi(\d+)ELi(\d+)E", asm, re.M))
+    assert built == {("64", "64"), ("128", "256")}
 
 
 @pytest.mark.parametrize("t,e,a,c,tile", KERNELS)
@@ -183,3 +190,49 @@ def test_regroup16():
         assert lo == [(l & 15, 8 * (l >> 4) + 2 * e) for l in range(64)]
         assert hi == [(l & 15, 8 * (l >> 4) + 4 + 2 * e) for l in range(64)]
         assert swap(*swap(lo, hi, 16), 32) == (x, y)
+
+
+@pytest.mark.parametrize("tile", ["Tile128", "Tile64"])
+@pytest.mark.parametrize("KP", [32, 16032])
+def test_blocked_fp32_loader_fetches_the_mn_loaders_pieces(tile, KP):
+    """fp32 blocked A: load j of wave w, lane l fetches the piece (K-row, ids) that the MN-contiguous loader puts
+    in the same LDS slot, inside the descriptor's range (the tile's ids in the K-tile's one token block), and the
+    fragment reads find their rows."""
+    bm, _, wm, wn = TILES[tile]
+    kw, nl, esz, pitch = wm * wn, bm // (8 * wm * wn), 4, 4 * bm
+    lanes, rows = pitch // 16, 1024 // pitch
+    stored = {}
+    for w in range(kw):
+        for j in range(nl):
+            for l in range(64):
+                kr = 32 // kw * w + l // lanes
+                off = kr * 16 + j * rows * 16 + ((l % lanes) << 9)
+                assert _blocked_decode(off, KP, esz) == (kr + rows * j, 4 * (l % lanes))
+                assert off + 16 <= bm * esz * 32
+                for e in range(4):
+                    stored[(nl * w + j) * 1024 + 16 * l + 4 * e] = (kr + rows * j, 4 * (l % lanes) + e)
+    assert len(stored) == 32 * bm
+    for m in range(wm):
+        wsub = m * (bm // wm)
+        for i in range(bm // wm // 16):
+            for u in range(2):
+                for l in range(64):
+                    for s in range(4):
+                        at = 4 * (l >> 4) * pitch + (wsub + (l & 15)) * 4 + (16 * u + s) * pitch + 64 * i
+                        assert stored[at] == (16 * u + 4 * (l >> 4) + s, wsub + 16 * i + (l & 15))
+
+
+@pytest.mark.parametrize("esz", [2, 4])
+def test_lse_epilogue_stores_e_blocked(esz):
+    """The LSE_BWD epilogue of a wave at (mw, nw): the token and first id of every 16-byte piece that lane l stores
+    for blocks i (16-bit: i and i + 1) and j."""
+    KP = 64 if esz == 2 else 128
+    for mw, nw in ((0, 0), (32, 32), (128, 192), (768, 224)):
+        for j in range(4):
+            for i in range(0, 8, 2 if esz == 2 else 1):
+                for l in range(64):
+                    g, r16 = l >> 4, l & 15
+                    e_blk = ((nw + 16 * j) >> 5) * KP * 1024 + (l >> 5) * 1024 + ((g & 1) * 32 + r16 + 16 * (j & 1)) * 16
+                    off = e_blk + ((mw + 16 * i) >> (4 if esz == 2 else 3)) * 1024
+                    ids = 8 * g if esz == 2 else 4 * g  # 16-bit: after regroup16, 8 ids of the 32 of two blocks
+                    assert _blocked_decode(off, KP, esz) == (nw + 16 * j + r16, mw + 16 * i + ids)
