@@ -77,7 +77,8 @@ typedef enum { LCE_REDUCTION_NONE = 0, LCE_REDUCTION_MEAN = 1, LCE_REDUCTION_SUM
  * Bytes of device workspace needed by lce_forward (with_backward = 0) or lce_forward_backward
  * (with_backward = 1) for these sizes. chunk_tokens is the number of tokens processed per chunk
  * (0 = automatic: with backward, all N tokens up to min(H, 2048), else min(H rounded down to 64,
- * N/2 rounded up to 64), at least 64, raised to ceil(N / limit) rounded up to 64 when that keeps the
+ * N/2 rounded up to 64), at least 64 (where such a chunk's blocked copies of X would pass 2^31 bytes,
+ * N/2 rounded down to 64 instead), raised to ceil(N / limit) rounded up to 64 when that keeps the
  * chunk count within dW's carry limit (BF16 4, FP16 9; see lce_plan_info) and is at most 2 H;
  * forward only, all N tokens up to 16384, else chunks of 16384 or the backward size if larger;
  * a nonzero value smaller than N must be a multiple of 64). The workspace holds
@@ -162,9 +163,9 @@ lce_status_t lce_forward(const void* hidden, const void* weight, const int64_t* 
  *     one per device, held from the library's first use on that device until the process ends.
  *     The call picks the largest chunk of tokens whose workspace fits it (the results do not depend
  *     on the chunk; where 64 tokens fit only with partial sums of 128 vocabulary rows instead of 32,
- *     V in the millions, they may differ from lce_forward's in the last bits) and returns LCE_ERR_WORKSPACE_TOO_SMALL, before anything is enqueued, when even
- *     64 tokens per chunk need more (the per-token part is 12 N bytes: N up to about 5 million at
- *     H = 4096, V = 128256).
+ *     V in the millions, they may differ from lce_forward's in the last bits) and returns
+ *     LCE_ERR_WORKSPACE_TOO_SMALL, before anything is enqueued, when even 64 tokens per chunk need more
+ *     (the per-token part is 12 N bytes: N up to about 5 million at H = 4096, V = 128256).
  *   - The array is shared by every call on a device and keeps the last call's contents (nothing in
  *     it has to start at zero). Calls that overlap on one device -- on different streams, or from
  *     different threads without ordering -- race on it: the caller orders them (one stream, or

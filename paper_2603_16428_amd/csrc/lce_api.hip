@@ -120,7 +120,7 @@ struct Plan {
   int64_t slices = 0;
   int dh_splits = 1;
   int64_t dh_kps = 0;             // K (vocabulary) per dH split, multiple of the K-tile
-  int64_t dw_run = 0;             // tokens per running sum of dW, multiple of the K-tile
+  int64_t dw_run = 0;             // tokens per running sum of a chunk's dW, multiple of the K-tile
   // dW's running sum over chunks in an fp32 accumulator instead of dW's own 16-bit type (more
   // chunks than carry_chunks() allows for the type).
   bool dw_acc32 = false;
@@ -253,10 +253,10 @@ bool dtype_ok(int dtype) { return dtype == LCE_DTYPE_FP32 || dtype == LCE_DTYPE_
 // counts as 1 us: at sizes where its few us matter the alternatives are as close.)
 // A split has to win by 5% (at nearly full grids the clock makes up for idle CUs), and its
 // partials stay below the size of W (or 64 MB), with the caller's own chunk_tokens, which asks for little
-// memory where it is small, below the size of the chunk's e (or eight splits). Of the 256 x 256 kernels, the eight waves of Tile256
-// are ahead (H = 4096, V = 128256, 4096 tokens: 2.84 ms against 2.94), gemm_xb_kernel only for narrow H
-// and long K (H = 768, V = 128256, 2048 tokens: 0.342 ms against 0.358). 16-bit Tile128 is for small
-// grids, which it cuts finer in fewer splits (H = 768, V = 50257, 1024 tokens: 75 us in ten splits
+// memory where it is small, below the size of the chunk's e (or eight splits). Of the 256 x 256 kernels,
+// the eight waves of Tile256 are ahead (H = 4096, V = 128256, 4096 tokens: 2.84 ms against 2.94),
+// gemm_xb_kernel only for narrow H and long K (H = 768, V = 128256, 2048 tokens: 0.342 ms against
+// 0.358). 16-bit Tile128 is for small grids, which it cuts finer in fewer splits (H = 768, V = 50257, 1024 tokens: 75 us in ten splits
 // against 81 in Tile256's 21); with more tokens or columns its operand traffic takes that back
 // (H = 12288, V = 32768, 2048 tokens: 1.27 ms unsplit, Tile256 in two splits the same; H = 4096,
 // V = 128256, 2048 tokens: 1.63 against 1.51).
@@ -311,8 +311,9 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
   if (H % (16 / p.esz) != 0) return LCE_ERR_UNSUPPORTED;
   const int64_t lim = (int64_t(1) << 31) - 1;
   // Automatic chunks: a training step keeps one chunk's e/dZ, so its chunks stay small; a forward
-  // call keeps only per-slice partials (N V / 16 bytes, of 32-row slices N V / 4), so it takes up to 16384 tokens at once
-  // (one launch of the logits GEMM instead of several, each with a partly empty last wave).
+  // call keeps only per-slice partials (N V / 16 bytes, in the 64 x 64 tile's 32-row slices N V / 4),
+  // so it takes up to 16384 tokens at once (one launch of the logits GEMM instead of several, each with
+  // a partly empty last wave).
   auto copies_fit = [&](int64_t tokens) {  // 32-bit limits of a chunk's two blocked copies of X
     if (tokens > lim || H > lim) return false;
     const int64_t xk = round_up(tokens, 64) / 32 * (round_up(H * p.esz, kTileBytes) / 32);

@@ -22,8 +22,8 @@
 // A's fragments: for the 32x32x16 bf16 MFMA a lane supplies 8 consecutive K of one row. K-contig
 // tiles give them with one ds_read_b128; MN-contig bf16 tiles with two ds_read_b64_tr_b16 (each
 // 16-lane group reads four K-rows of 16 columns and the LDS transposes them so that lane j
-// receives column j of the four rows). The 16-byte slots of every LDS row are XOR-swizzled so that these reads are free of bank conflicts. A
-// blocked A is fetched into the very LDS slots an MN-contig one would occupy. Fragments are
+// receives column j of the four rows). The 16-byte slots of every LDS row are XOR-swizzled so that
+// these reads are free of bank conflicts. A blocked A's fragments go into LDS whole. Fragments are
 // double-buffered in registers: the reads for the next 32 bytes of K are in flight while the
 // MFMAs of the current ones run.
 //
@@ -79,7 +79,7 @@ struct GemmArgs {
   const void* B;
   int64_t lda, ldb;   // pitches in elements
   int M, N, K;        // K-contig operands need K to be a multiple of 16 bytes' worth
-  int tiles_m, tiles_n, splits, k_per_split;  // k_per_split: a multiple of the K-tile
+  int tiles_m, tiles_n, splits, k_per_split;  // k_per_split (fp32 dW: K per run): a multiple of the K-tile
   int group_m;        // tile rows per raster group
   // epilogue
   void* out;          // LSE_BWD: e, blocked (ldo = K-pairs per token block, covering M rounded up
@@ -88,7 +88,7 @@ struct GemmArgs {
   float* pmax;        // LSE: [slices, ldp]
   float* psum;
   int64_t ldp;
-  int mode;           // DW: DwMode; STORE: 1 = fp32 split-K partials at out + split * M * ldo
+  int mode;           // DW: DwMode; STORE: 1 = fp32 split-K partials at out + split * N * ldo
   const int* n_valid; // STORE (mode 0) / DW of 16-bit types whose dz is stored unscaled: the
   int mean;           // valid-token count and reduction that give g (see Storage)
   // LSE_BWD, target-referenced (ref != nullptr; chunk-offset, like the columns): ref[col] is the

@@ -8,18 +8,24 @@ import torch
 
 from paper_2603_16428_amd import lce
 
+DTYPES = {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}
+
 
 @pytest.mark.parametrize("N,H,dtype,chunk", [
     (1, 64, "bf16", 1), (1000, 4096, "bf16", 1000), (2048, 2048, "bf16", 2048), (2048, 4096, "fp16", 2048),
     (2049, 4096, "bf16", 1088), (3000, 4096, "bf16", 1536), (256, 256, "fp32", 256), (257, 256, "fp32", 192),
     (129, 8, "bf16", 64), (1000, 768, "bf16", 512), (4096, 768, "bf16", 1024), (8192, 4096, "bf16", 4096)])
 def test_auto_chunk(N, H, dtype, chunk):
-    dt = {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype]
+    dt = DTYPES[dtype]
     assert lce.auto_chunk_tokens(N, H, 5000, dt) == chunk
     info = lce.plan_info(N, H, 5000, dt)
     assert info["chunk_tokens"] == chunk and info["chunks"] == -(-N // chunk)
     # e is no larger than W (twice W where that avoids the fp32 carry), but for the 64-token minimum.
     assert chunk <= max(64, H, 2 * H if -(-N // H) > 4 and dtype == "bf16" else 0)
+
+
+def _log_uniform(rng, lo, hi):
+    return int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
 
 
 def _fp32_chunk(N, H):
@@ -45,7 +51,7 @@ def test_fp32_dh_splits(N, H, V):
 def test_fp32_dh_splits_over_the_range():
     rng = random.Random(7)
     for _ in range(2000):
-        N, H, V = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((64, 16384), (32, 1536), (4096, 152064)))
+        N, H, V = (_log_uniform(rng, *r) for r in ((64, 16384), (32, 1536), (4096, 152064)))
         assert lce.plan_info(N, 8 * H, V, torch.float32)["dh_splits"] >= _fp32_splits(N, 8 * H), (N, 8 * H, V)
 
 
@@ -54,7 +60,7 @@ def test_fp32_dh_splits_over_the_range():
     (1100, 1048576, 1000, "bf16", 512), (65, 4000000, 5, "bf16", 65)])
 def test_wide_rows_are_accepted(N, H, V, dtype, chunk):
     """Rows so wide that one chunk's blocked copies would pass 2^31 bytes: chunks of half the tokens."""
-    dt = {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype]
+    dt = DTYPES[dtype]
     assert lce.plan_info(N, H, V, dt)["chunk_tokens"] == chunk
     assert lce.workspace_size(N, H, V, dt) > 0
 
@@ -71,14 +77,15 @@ def test_dh_partials_stay_within_their_bound():
     rng = random.Random(13)
     cases = [(203, 5472, 135757, "fp32", 0), (8192, 4096, 128256, "bf16", 64), (4096, 768, 50257, "bf16", 64)]
     for _ in range(2000):
-        N, H, V = (int(math.exp(rng.uniform(math.log(lo), math.log(hi)))) for lo, hi in ((64, 16384), (32, 1536), (64, 152064)))
-        cases.append((N, 8 * H, V, rng.choice(("bf16", "fp16", "fp32")), rng.choice((0, 64, 64 * rng.randint(1, 64)))))
+        N, H, V = (_log_uniform(rng, *r) for r in ((64, 16384), (32, 1536), (64, 152064)))
+        cases.append((N, 8 * H, V, rng.choice(tuple(DTYPES)), rng.choice((0, 64, 64 * rng.randint(1, 64)))))
     for N, H, V, dtype, chunk in cases:
         size = 4 if dtype == "fp32" else 2
-        info = lce.plan_info(N, H, V, {"bf16": torch.bfloat16, "fp16": torch.float16, "fp32": torch.float32}[dtype], True, chunk)
+        info = lce.plan_info(N, H, V, DTYPES[dtype], True, chunk)
         if info["dh_splits"] == 1:
             continue
         tokens = info["chunk_tokens"]
         part, eight = info["dh_splits"] * tokens * H * 4, 8 * tokens * H * 4
         e = -(-tokens // 64) * 64 * -(-V // 256) * 256 * size
-        assert part <= (max(e, eight) if chunk else max(64 << 20, V * H * size, eight if dtype == "fp32" else 0)), (N, H, V, dtype, chunk)
+        bound = max(e, eight) if chunk else max(64 << 20, V * H * size, eight if dtype == "fp32" else 0)
+        assert part <= bound, (N, H, V, dtype, chunk)

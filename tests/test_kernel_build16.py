@@ -232,7 +232,8 @@ def test_lse_epilogue_stores_e_blocked(esz):
             for i in range(0, 8, 2 if esz == 2 else 1):
                 for l in range(64):
                     g, r16 = l >> 4, l & 15
-                    e_blk = ((nw + 16 * j) >> 5) * KP * 1024 + (l >> 5) * 1024 + ((g & 1) * 32 + r16 + 16 * (j & 1)) * 16
+                    e_blk = ((nw + 16 * j) >> 5) * KP * 1024 + (l >> 5) * 1024
+                    e_blk += ((g & 1) * 32 + r16 + 16 * (j & 1)) * 16
                     off = e_blk + ((mw + 16 * i) >> (4 if esz == 2 else 3)) * 1024
                     ids = 8 * g if esz == 2 else 4 * g  # 16-bit: after regroup16, 8 ids of the 32 of two blocks
                     assert _blocked_decode(off, KP, esz) == (nw + 16 * j + r16, mw + 16 * i + ids)
