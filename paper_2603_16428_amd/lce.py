@@ -268,18 +268,22 @@ def _bytes_are_values(t) -> bool:
     """Whether t is a plain tensor whose values are what its memory holds: not a subclass's or a batched one
     (of torch.func or of is_grads_batched: no storage), not a lazily negated view (an imaginary part of a
     conjugate), whose bytes have the other sign, nor a zero tensor, which has no memory at all."""
-    if type(t) is not torch.Tensor or t.layout != torch.strided:
+    if type(t) is not torch.Tensor or t.is_neg():
         return False
     try:
-        t.untyped_storage()
-    except (NotImplementedError, RuntimeError):
+        return t.data_ptr() != 0 or (t.numel() == 0 and t.layout == torch.strided)
+    except (NotImplementedError, RuntimeError):  # no storage: batched, sparse
         return False
-    return not t.is_neg() and (t.data_ptr() != 0 or t.numel() == 0)
 
 
-def _differentiated(t) -> bool:
-    """Whether autograd follows t here: a graph (double backward), or a forward-mode tangent."""
-    return (torch.is_grad_enabled() and t.requires_grad) or torch.autograd.forward_ad.unpack_dual(t).tangent is not None
+def _differentiated(tensors) -> bool:
+    """Whether autograd follows one of the tensors here: a graph (double backward), or a forward-mode tangent."""
+    if torch.is_grad_enabled() and any(t.requires_grad for t in tensors):
+        return True
+    # Without an active level there are no tangents, and nothing to ask (0: this torch does not say).
+    if getattr(torch.autograd.forward_ad, "_current_level", 0) < 0:
+        return False
+    return any(torch.autograd.forward_ad.unpack_dual(t).tangent is not None for t in tensors)
 
 
 def _scaled(grad_out, grads):
@@ -290,8 +294,9 @@ def _scaled(grad_out, grads):
     tensors that saved-tensor hooks changed) goes through torch's own operators.
     """
     g = grad_out.to(torch.float32)
-    plain = (_dispatch_modes is not None and _dispatch_modes() == 0
-             and all(_bytes_are_values(t) and not _differentiated(t) for t in (g, *grads)) and g.numel() == 1)
+    tensors = (g, *grads)
+    plain = (_dispatch_modes is not None and _dispatch_modes() == 0 and all(map(_bytes_are_values, tensors))
+             and not _differentiated(tensors) and g.numel() == 1)
     dt = grads[0].dtype
     if not (plain and dt in DTYPES and all(
             t.is_cuda and t.device == g.device and t.dtype == dt and t.is_contiguous() and t.data_ptr() % 16 == 0
