@@ -120,7 +120,7 @@ struct Plan {
   int64_t slices = 0;
   int dh_splits = 1;
   int64_t dh_kps = 0;             // K (vocabulary) per dH split, multiple of the K-tile
-  int64_t dw_run = 0;             // tokens per running sum of a chunk's dW, multiple of the K-tile
+  int64_t dw_run = 0;             // tokens per running sum of a chunk's dW, multiple of two K-tiles
   // dW's running sum over chunks in an fp32 accumulator instead of dW's own 16-bit type (more
   // chunks than carry_chunks() allows for the type).
   bool dw_acc32 = false;
@@ -363,7 +363,7 @@ lce_status_t make_plan(int64_t N, int64_t H, int64_t V, int dtype, bool backward
     const int64_t kblocks = cdiv(V, kbk);
     const int64_t fp32_tokens = chunk_tokens == 0 ? half_chunk(N, H) : nc;
     plan_dh(p, kblocks, fp32_tokens, chunk_tokens != 0);
-    p.dw_run = round_up(p.esz == 4 ? cdiv(nc, cdiv(nc, fp32_tokens)) : nc, kbk);
+    p.dw_run = round_up(p.esz == 4 ? cdiv(nc, cdiv(nc, fp32_tokens)) : nc, 2 * kbk);
     p.dh_kps = cdiv(kblocks, p.dh_splits) * kbk;
     p.tile_dw = dw_tile(nc, H, V, p.esz);
     p.dw_acc32 = p.esz == 2 && p.chunks > carry_chunks(p.esz, dtype);

@@ -440,7 +440,17 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& g, f32x4 (&acc)[
 // registers, four K-quads of fragments, three ahead. A K-tile is four sections, K-quad p/2 by half p%2
 // of the wave's row blocks; each section's A fragments are read during the one before it, and it issues
 // a quarter of A's K-tile three ahead and half of B's fragments three K-quads ahead.
-// run: the run-th k_per_split of K (fp32 dW, see gemm_xs_kernel; else 0).
+// fp32 dW is summed in runs of k_per_split tokens (an even number of K-tiles), one after the other: an
+// entry's rounding error grows with the length of its running sum (2048 tokens, H = 2048: 7.7e-7 in one run,
+// 5.5e-7 in two of half of them). 64 x 64 tiles have the registers for the sum of the earlier runs beside
+// the accumulators (256 x 256 x 4096: a second pass over the pipeline cost 3 us of 43, this nothing); the
+// others' kernel takes one run after the other through here, each added to dW.
+template <typename T, int EPI, typename C>
+constexpr bool kRunsInRegisters = EPI == EPI_DW && sizeof(T) == 4 && C::kBM == 64;
+template <typename T, int EPI, typename C>
+constexpr bool kRunsThroughDw = EPI == EPI_DW && sizeof(T) == 4 && C::kBM != 64;
+
+// run: which run of K (kRunsThroughDw, else 0).
 template <typename T, int EPI, int AL, bool KCHECK, typename C>
 __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, int run, char* smem) {
   constexpr int kEsz = (int)sizeof(T);
@@ -461,8 +471,9 @@ __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, int run
   const int split = rest / g.tiles_n;
   const int m0 = tm * C::kBM, n0 = tn * C::kBN;
   const int mw = m0 + wm * 16 * NI, nw = n0 + wn * 16 * NJ;
-  const int kb = (split + run) * g.k_per_split;
-  const int ke = min(g.K, kb + g.k_per_split);
+  constexpr bool kRegRuns = kRunsInRegisters<T, EPI, C>;
+  const int kb = kRegRuns ? 0 : (split + run) * g.k_per_split;
+  const int ke = kRegRuns ? g.K : min(g.K, kb + g.k_per_split);
 
   using Op = Operand16<T, AL, C>;
   Op opa;
@@ -647,18 +658,42 @@ __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, int run
     load_b(2, std::integral_constant<int, 2>{}, H1{});
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kNL * (kXbAhead - 1) + 3 * NJ) : "memory");
     read_frags(H0{}, H0{}, H0{}, std::false_type{}, 0);
-    for (int kt = 0; kt < nk; kt += 2) {  // an odd count runs one more K-tile of zeros
-      section(kt, std::integral_constant<int, 0>{});
-      section(kt, std::integral_constant<int, 1>{});
-      section(kt, std::integral_constant<int, 2>{});
-      section(kt, std::integral_constant<int, 3>{});
-      section(kt, std::integral_constant<int, 4>{});
-      section(kt, std::integral_constant<int, 5>{});
-      section(kt, std::integral_constant<int, 6>{});
-      section(kt, std::integral_constant<int, 7>{});
+    if constexpr (kRegRuns) {  // as below, run by run
+      f32x4 sum[NI][NJ] = {};
+      for (int kt = 0; kt < nk;) {
+        const int end = min(nk, kt + g.k_per_split / kBK);
+        for (; kt < end; kt += 2) {
+          for_each_index([&](auto s) { section(kt, s); }, std::make_integer_sequence<int, 8>{});
 #pragma unroll
-      for (int k = 0; k < Op::kXa; ++k) opa.xa[k] += pair_delta;
-      pair_delta = 0u - pair_delta;
+          for (int k = 0; k < Op::kXa; ++k) opa.xa[k] += pair_delta;
+          pair_delta = 0u - pair_delta;
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            sum[i][j] += acc[i][j];
+            acc[i][j] = (f32x4){};
+          }
+      }
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = sum[i][j];
+    } else {
+      for (int kt = 0; kt < nk; kt += 2) {  // an odd count runs one more K-tile of zeros
+        section(kt, std::integral_constant<int, 0>{});
+        section(kt, std::integral_constant<int, 1>{});
+        section(kt, std::integral_constant<int, 2>{});
+        section(kt, std::integral_constant<int, 3>{});
+        section(kt, std::integral_constant<int, 4>{});
+        section(kt, std::integral_constant<int, 5>{});
+        section(kt, std::integral_constant<int, 6>{});
+        section(kt, std::integral_constant<int, 7>{});
+#pragma unroll
+        for (int k = 0; k < Op::kXa; ++k) opa.xa[k] += pair_delta;
+        pair_delta = 0u - pair_delta;
+      }
     }
     // Loads past the end may still be in flight (they target no memory), and the last section's
     // fragment reads; their LDS and registers must not be reused before they retire.
@@ -668,15 +703,12 @@ __device__ __forceinline__ void gemm_xs_tile(const GemmArgs& g, int bid, int run
   gemm_epilogue16<T, EPI, kPreload>(g, acc, mw, nw, split, n0, smem + kXbASlots * C::kSlot, run > 0);
 }
 
-// fp32 dW in runs of k_per_split tokens, one after the other, each added to the sum of the earlier ones in
-// dW: an entry's rounding error grows with the length of its running sum (2048 tokens, H = 2048: 7.7e-7 in
-// one run, 5.5e-7 in two of half of them).
 
 template <typename T, int EPI, int AL, bool KCHECK, typename C>
 __global__ __launch_bounds__(C::kThreads, C::kBM == 256 ? 1 : C::kBM == 128 ? 2 : 4) void gemm_xs_kernel(const GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   if (g.run_if != nullptr && __builtin_amdgcn_readfirstlane(*g.run_if) == 0) return;
-  if constexpr (EPI == EPI_DW && sizeof(T) == 4) {
+  if constexpr (kRunsThroughDw<T, EPI, C>) {
     for (int run = 0; run * g.k_per_split < g.K; ++run) {
       // Every wave is done with the ring, and the tile's stores no longer count in vmcnt.
       if (run > 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
